@@ -11,11 +11,12 @@ namespace gm {
 // residual and stores the weighted residual R = w r (FP32) of every pixel in
 // rb; the magnitude (DER) and analytic (sky) columns take their products
 // from the convolved light and the pixel position there.  Pass 2 correlates R
-// with the PSF -- a convolution with the flipped PSF psf_t, zero padding as in
-// the forward model -- into Q and adds Q dI/du_k with the unconvolved,
+// with the PSF -- a convolution with the flipped PSF, zero padding as in the
+// forward model -- into Q and adds Q dI/du_k with the unconvolved,
 // pixel-integrated derivatives of the light: sum_pixels R (PSF x D_k) =
 // sum_pixels (PSF-correlated R) D_k.  rb holds H W floats; it is read back
-// through L2 (agent-scope loads) after the workgroup barrier.
+// through L2 (agent-scope loads) after the workgroup barrier.  psl: the PSF's
+// LDS copy (both passes).
 __device__ inline float load_l2(const float *p)
 {
     return __uint_as_float(__hip_atomic_load(reinterpret_cast<const unsigned int *>(p), __ATOMIC_RELAXED,
@@ -24,7 +25,7 @@ __device__ inline float load_l2(const float *p)
 
 template <class F, int KT, int NG>
 __device__ void evaluate_grad(const double *u, const ModelArgs &ma, const BatchArgs &ba, const Meta &me,
-                              EvalShared<F> &sh, float *planes, const cfloat *psf_t, float *rb, double *out_chi2,
+                              EvalShared<F> &sh, float *planes, const float *psl, float *rb, double *out_chi2,
                               double *out_g)
 {
     constexpr int P = F::P;
@@ -45,12 +46,10 @@ __device__ void evaluate_grad(const double *u, const ModelArgs &ma, const BatchA
     for (int ty = 0; ty < nty; ++ty) {
         for (int tx = 0; tx < ntx; ++tx) {
             const int ti0 = ty * TILE, tj0 = tx * TILE;
-            fill_region<F, 0, 1>(sh, planes, H, W, K, ti0, tj0);
+            fill_region<F, 0, 1, shift64<KT>()>(sh, planes, H, W, K, ti0, tj0);
             __syncthreads();
             double acc0[4];
-            const double *base = reinterpret_cast<const double *>(planes) + 4 * cg;
-            if constexpr (KT > 0) conv_plane<KT, double>(base, r, IWP, psf, acc0);
-            else conv_plane_any<double>(base, r, K, IWP, psf, acc0);
+            conv64<KT>(planes, K, psf, psl, r, cg, acc0);
             __syncthreads();
             const int i = ti0 + r;
             if (i >= H) continue;
@@ -91,9 +90,14 @@ __device__ void evaluate_grad(const double *u, const ModelArgs &ma, const BatchA
                 planes[ri * IWP + ci] = (gi >= 0 && gi < H && gj >= 0 && gj < W) ? load_l2(rb + gi * W + gj) : 0.0f;
             }
             __syncthreads();
-            float q4[4];
-            if constexpr (KT > 0) conv_plane<KT, float>(planes + 4 * cg, r, IWP, psf_t, q4);
-            else conv_plane_any<float>(planes + 4 * cg, r, K, IWP, psf_t, q4);
+            f32x4 q4;
+            const float *rp = planes + 4 * cg + (r + K - 1) * IWP;
+            if constexpr (KT > 0) {
+                conv_one<KT, true>(rp, psl, q4);
+            } else {
+                f32x4 none;
+                conv_any<false, true>(rp, K, IWP, psl, none, q4);
+            }
             __syncthreads();
             const int i = ti0 + r;
             if (i >= H) continue;
@@ -114,12 +118,12 @@ __device__ void evaluate_grad(const double *u, const ModelArgs &ma, const BatchA
     double *sred = reinterpret_cast<double *>(planes);
     const int lane = tid & 63, wave = tid >> 6;
     {
-        double v = wave_sum(c2);
+        double v = strip_sum(c2, K);
         if (lane == 0) sred[wave * NR] = v;
     }
 #pragma unroll
     for (int q = 1; q < NR; ++q) {
-        double v = wave_sum((double)red[q - 1]);
+        double v = strip_sum((double)red[q - 1], K);
         if (lane == 0) sred[wave * NR + q] = v;
     }
     __syncthreads();
@@ -130,21 +134,6 @@ __device__ void evaluate_grad(const double *u, const ModelArgs &ma, const BatchA
         else out_g[q - 1] = sm;
     }
     __syncthreads();
-}
-
-// The PSF of every galaxy flipped in both axes (the correlation kernel of the
-// adjoint): psf_t[off + (K-1-a) K + (K-1-b)] = psf[off + a K + b].  One
-// workgroup per galaxy; galaxies that share a PSF write the same values.
-static __global__ void flip_psf_kernel(const Meta *meta, int n_gal, const float *psf, float *psf_t)
-{
-    const int g = blockIdx.x;
-    if (g >= n_gal) return;
-    const Meta me = meta[g];
-    const int K = me.k, n = K * K;
-    for (int e = threadIdx.x; e < n; e += blockDim.x) {
-        const int a = e / K, b = e - a * K;
-        psf_t[me.psf_off + (int64_t)(K - 1 - a) * K + (K - 1 - b)] = psf[me.psf_off + e];
-    }
 }
 
 // ---------------------------------------------------------------- gradient descent (Adam)
@@ -164,13 +153,12 @@ struct AdamArgs {
     int *status;
     int steps;
     double lr, beta1, beta2, eps;
-    const float *psf_t;     // flipped PSFs, same offsets as the PSFs
     float *rbuf;            // weighted residuals: rstride floats per workgroup
     int64_t rstride;
 };
 
 template <class F, int KT, int NG>
-__global__ __launch_bounds__(NT, (min_wg<F, KT, NG>())) void adam_fit_kernel(ModelArgs ma, BatchArgs ba, AdamArgs aa)
+__global__ __launch_bounds__(NT, 2) void adam_fit_kernel(ModelArgs ma, BatchArgs ba, AdamArgs aa)
 {
     extern __shared__ float4 dyn_lds[];
     float *planes = reinterpret_cast<float *>(dyn_lds);
@@ -189,14 +177,14 @@ __global__ __launch_bounds__(NT, (min_wg<F, KT, NG>())) void adam_fit_kernel(Mod
             load_u<F>(s, ma, aa.params + (int64_t)g * ma.p);
             clamp_u<F>(s.u, me.h, me.w);
         }
+        const float *psl = stage_psf<F, NG>(planes, ba.psf + uniform64(me.psf_off), me.k);
         __syncthreads();
-        const cfloat *psf_t = (const cfloat *)(aa.psf_t + uniform64(me.psf_off));
         float *rb = aa.rbuf + (int64_t)blockIdx.x * aa.rstride;
         // moments of lane k (k < P): registers of the first wave
         double m1 = 0.0, m2 = 0.0, b1t = 1.0, b2t = 1.0;
         bool bad = false;
         for (int t = 1; t <= aa.steps && !bad; ++t) {
-            evaluate_grad<F, KT, NG>(s.u, ma, ba, me, esh, planes, psf_t, rb, &s.chi2, s.g);
+            evaluate_grad<F, KT, NG>(s.u, ma, ba, me, esh, planes, psl, rb, &s.chi2, s.g);
             bad = !isfinite(s.chi2);
             if (!bad && tid < P && s.freev[tid]) {
                 const double grad = -2.0 * s.g[tid];
@@ -209,7 +197,7 @@ __global__ __launch_bounds__(NT, (min_wg<F, KT, NG>())) void adam_fit_kernel(Mod
             }
             __syncthreads();
         }
-        if (!bad) evaluate_grad<F, KT, NG>(s.u, ma, ba, me, esh, planes, psf_t, rb, &s.chi2, s.g);
+        if (!bad) evaluate_grad<F, KT, NG>(s.u, ma, ba, me, esh, planes, psl, rb, &s.chi2, s.g);
         if (tid == 0) {
             double nat[P];
             canonical_nat<F>(s.u, s.freev, nat);
@@ -223,13 +211,11 @@ __global__ __launch_bounds__(NT, (min_wg<F, KT, NG>())) void adam_fit_kernel(Mod
     }
 }
 
-// psf_len: floats of the PSF array the batch reads (0 for an unconvolved
-// model, which runs with the unit PSF); max_px: the largest cutout.  The
-// context's scratch holds the flipped PSFs, then one residual image of max_px
-// floats per workgroup of the grid.
+// max_px: the largest cutout.  The context's scratch holds one residual image
+// of max_px floats per workgroup of the grid.
 template <class F, int NG, int KT>
 int launch_adam(gm_ctx *c, const ModelArgs &ma, const BatchArgs &ba, AdamArgs aa, size_t lds, int wpc,
-                int64_t psf_len, int64_t max_px, hipStream_t st)
+                int64_t max_px, hipStream_t st)
 {
     auto kern = adam_fit_kernel<F, KT, NG>;
     int per_cu;
@@ -237,19 +223,10 @@ int launch_adam(gm_ctx *c, const ModelArgs &ma, const BatchArgs &ba, AdamArgs aa
     if (rc) return rc;
     if (wpc > 0) per_cu = std::min(per_cu, wpc);
     int grid = std::min(aa.n_gal, per_cu * c->num_cu);
-    const int64_t psf_al = (psf_len + 63) / 64 * 64;
     aa.rstride = (max_px + 63) / 64 * 64;
     void *ws;
-    if ((rc = ensure_aux(c, sizeof(float) * (size_t)(psf_al + aa.rstride * grid), &ws))) return rc;
-    float *wsf = reinterpret_cast<float *>(ws);
-    if (psf_len > 0) {
-        hipLaunchKernelGGL(flip_psf_kernel, dim3(aa.n_gal), dim3(256), 0, st, ba.meta, aa.n_gal, ba.psf, wsf);
-        if ((rc = hip_rc(hipGetLastError()))) return rc;
-        aa.psf_t = wsf;
-    } else {
-        aa.psf_t = ba.psf;      // the unit PSF is its own flip
-    }
-    aa.rbuf = wsf + psf_al;
+    if ((rc = ensure_aux(c, sizeof(float) * (size_t)(aa.rstride * grid), &ws))) return rc;
+    aa.rbuf = reinterpret_cast<float *>(ws);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, ma, ba, aa);
     return hip_rc(hipGetLastError());
 }
@@ -287,13 +264,9 @@ int run_adam(gm_ctx *c, const CallInfo &ci, const gm_adam_opts *o, double *param
     aa.beta1 = o->beta1;
     aa.beta2 = o->beta2;
     aa.eps = o->eps;
-    int64_t psf_len = 0, max_px = 0;
-    for (int g = 0; g < b->n_gal; ++g) {
-        if (ci.convolved) psf_len = std::max(psf_len, b->psf_off[g] + (int64_t)b->psf_k[g] * b->psf_k[g]);
-        max_px = std::max(max_px, (int64_t)b->h[g] * b->w[g]);
-    }
-    return Dispatch<F, NG, KTS...>::adam(batch_kt(ci), c, ci.ma, batch_args(c, ci, sg), aa, lds, ci.wpc, psf_len,
-                                         max_px, st);
+    int64_t max_px = 0;
+    for (int g = 0; g < b->n_gal; ++g) max_px = std::max(max_px, (int64_t)b->h[g] * b->w[g]);
+    return Dispatch<F, NG, KTS...>::adam(batch_kt(ci), c, ci.ma, batch_args(c, ci, sg), aa, lds, ci.wpc, max_px, st);
 }
 
 }  // namespace gm

@@ -137,6 +137,19 @@ __device__ inline double lane_value(double v, int lane)
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | (uint64_t)lo);
 }
 
+// The value of the lane 32 away.
+__device__ inline double other_half(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t l = (uint32_t)b, h = (uint32_t)(b >> 32);
+    const bool up = (threadIdx.x & 32) != 0;
+    const auto sl = __builtin_amdgcn_permlane32_swap(l, l, false, false);
+    const auto sh = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+    // first result: {lower, lower} halves; second: {upper, upper}
+    const uint32_t ol = up ? sl[0] : sl[1], oh = up ? sh[0] : sh[1];
+    return __builtin_bit_cast(double, ((uint64_t)oh << 32) | (uint64_t)ol);
+}
+
 // Sum over the 64 lanes of a wave; every lane gets the total.  Within each
 // 16-lane row a shift-and-add ladder (row_shr 1, 2, 4, 8) leaves the row sum
 // in the row's last lane; the four row sums are then added in row order.

@@ -5,10 +5,10 @@
 // derivatives with respect to every LM variable are evaluated on the tile's
 // (32 + K - 1)^2 input region straight into LDS, one plane per quantity; the
 // oversampled central window is evaluated once per model evaluation into a
-// small LDS table.  Each thread then convolves a 1 x 4 strip of outputs of
-// every plane with the PSF (true convolution, zero padding), streaming one
-// row segment from LDS per PSF row and reading the PSF through the scalar
-// cache; the results stay in registers.  When the planes of a model do not fit
+// small LDS table.  Each thread then owns a 1 x 4 strip of outputs of every
+// plane convolved with the PSF (true convolution, zero padding): the FP64
+// light by vector FMAs, the FP32 planes on the matrix cores, row segments and
+// taps from LDS; the results stay in registers.  When the planes of a model do not fit
 // LDS together (or fit only one workgroup per CU) they are processed in NG
 // groups, re-evaluating the profile per group (only the first group needs the
 // FP64 light).  The fitting kernel turns the convolved planes into residuals
@@ -69,10 +69,9 @@ __host__ __device__ constexpr int region_h(int K) { return TILE + K - 1; }
 __host__ __device__ constexpr int region_wp(int K) { return 28 + 4 * ((K + 3 + 3) / 4); }
 
 // FP64 light plane rows: with a pitch of 48 doubles (PSF side 15) the 16-byte
-// reads of two adjacent rows (one 16-lane group) fall on the same LDS banks;
-// odd rows stored 2 doubles (16 bytes) further on read conflict-free
-// (measured with the bank-conflict counter).  The pitch has the 2 spare
-// doubles this needs.
+// reads of two rows two apart (one 16-lane group, strip_of) fall on the same
+// LDS banks; rows with bit 1 set stored 2 doubles (16 bytes) further on read
+// conflict-free.  The pitch has the 2 spare doubles this needs.
 template <int KT>
 __host__ __device__ constexpr bool shift64()
 {
@@ -80,21 +79,39 @@ __host__ __device__ constexpr bool shift64()
 }
 
 // Output strip of thread tid in a tile: row r, columns 4 cg .. 4 cg + 3.  Wave
-// w covers rows 8w .. 8w + 7, 8 lanes per row.  When the row pitch is 8
-// (mod 16) floats (PSF sides 7, 9, 23, 25, ...), adjacent rows' 16-byte
-// segment reads overlap on three quarters of the LDS banks; the two 8-lane
-// halves of each 16-lane group then take rows 4 apart (4 x pitch = 32 mod 64),
-// which measured 6% faster fits at K = 25.  Other pitches keep rows in order
-// (the paired mapping measured 1% slower at K = 15).
-__host__ __device__ inline int strip_gap(int IWP) { return (IWP % 16 == 8) ? 4 : 0; }
+// w covers rows 8w .. 8w + 7, 8 lanes per row: lanes 0-31 the even rows, lanes
+// 32-63 the odd ones, so that lanes l and l + 32 own the two rows of a row
+// pair rp and the convolution can give each half of the wave a plane of its
+// own over both rows (conv_pair).  A 16-lane group (which reads LDS together)
+// holds row pairs rp and rp + 1, two rows apart: free of bank conflicts at a
+// pitch of 16 (mod 32) floats (side 15).  At a pitch of 8 (mod 16) floats
+// (sides 7, 9, 23, 25, 39, 41) it holds rp and rp + 2, four rows apart
+// (4 x pitch = 32 mod 64), which is conflict-free there.
+__host__ __device__ inline int strip_gap(int IWP) { return (IWP % 16 == 8) ? 4 : 2; }
 __device__ inline void strip_of(int tid, int K, int &r, int &cg)
 {
-    const int lane = tid & 63, w = tid >> 6, gi = lane >> 4, h = (lane >> 3) & 1;
+    const int lane = tid & 63, w = tid >> 6;
     cg = lane & 7;
-    int rb;
-    if (strip_gap(region_wp(K)) == 4) rb = gi + 4 * h;
-    else rb = lane >> 3;
-    r = 8 * w + rb;
+    const int gi = (lane >> 4) & 1, j = (lane >> 3) & 1;
+    const int rp = strip_gap(region_wp(K)) == 4 ? gi + 2 * j : 2 * gi + j;
+    r = 8 * w + 2 * rp + (lane >> 5);
+}
+
+// Sum of an FP64 value over a wave's strips, every lane gets the total: within
+// each row the eight strips by a shift-and-add ladder (row_shr 1, 2, 4), then
+// row 2i + 1 + row 2i (strip_gap 2) or row i + 4 + row i (strip_gap 4) for
+// i = 0..3, and those four sums in order.
+__device__ inline double strip_sum(double v, int K)
+{
+    v += dpp_move<0x111>(v);
+    v += dpp_move<0x112>(v);
+    v += dpp_move<0x114>(v);
+    if (strip_gap(region_wp(K)) == 4) {
+        v += dpp_move<0x118>(v);
+        return ((lane_value(v, 15) + lane_value(v, 47)) + lane_value(v, 31)) + lane_value(v, 63);
+    }
+    v += other_half(v);
+    return ((lane_value(v, 7) + lane_value(v, 15)) + lane_value(v, 23)) + lane_value(v, 31);
 }
 
 // Plane groups: plane 0 (FP64) counts two units, the others one; groups are
@@ -290,10 +307,10 @@ __device__ void fill_region(const EvalShared<F> &sh, float *buf, int H, int W, i
     // region rows r0..r1-1 and columns c0..c1-1 lie inside the image
     const int r0 = max(0, c - ti0), r1 = min(IH, H + c - ti0);
     const int c0 = max(0, c - tj0), c1 = min(IW, W + c - tj0);
-    // region point (ri, ci); SH: odd rows of the FP64 plane 2 further on
+    // region point (ri, ci); SH: rows with bit 1 set of the FP64 plane 2 further on
     auto store = [&](int ri, int ci, double v0, const float *dp) {
         const int idx = ri * IWP + ci;
-        if constexpr (LO == 0) b0[SH ? idx + 2 * (ri & 1) : idx] = v0;
+        if constexpr (LO == 0) b0[SH ? idx + (ri & 2) : idx] = v0;
 #pragma unroll
         for (int q = QLO; q < HI; ++q) bf[(q - QLO) * plane_sz + idx] = dp[q - 1];
     };
@@ -395,66 +412,64 @@ __device__ inline void row_part(const T *rp, PR pr, T &a0, T &a1, T &a2, T &a3)
     }
 }
 
-// Convolve one plane (elements of type T, row pitch IWP) for a 1 x 4 output
-// strip with a compile-time PSF side (the Adam fit's planes).  Up to side 15,
-// FP32 planes load the segment of the next PSF row while the current one is
-// used and the FP64 plane, whose segment is twice as large, loads one row at
-// a time.  Wider
-// PSFs take each row in two halves of taps, each with only the part of the
-// segment it reads, so that the kernel fits two workgroups' registers.
-template <int KT, typename T>
-__device__ inline void conv_plane(const T *base, int r, int IWP, const cfloat *psf, T (&out)[4])
+// Any PSF side, FP64: element by element of the row segment, from the far end
+// (each accumulator then sees its taps in increasing order), the four taps an
+// element meets sliding through registers; PSF rows from LDS (psl).
+__device__ inline void conv64_any(const double *base, int r, int K, int IWP, const float *psl, double (&out)[4])
 {
-    constexpr int PER = 16 / sizeof(T);
-    constexpr int SEG = ((KT + 3 + PER - 1) / PER) * PER;
-    T a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-    if constexpr (KT > 15) {
-        // taps v < VS read elements from ES on, taps v >= VS elements from 0
-        constexpr int ES = 4 * ((KT - 1) / 8), VS = KT - ES;
-#pragma unroll 1
-        for (int u = 0; u < KT; ++u) {
-            const T *rp = base + (r + KT - 1 - u) * IWP;
-            row_part<KT, 0, VS, ES>(rp, psf + u * KT, a0, a1, a2, a3);
-            row_part<KT, VS, KT, 0>(rp, psf + u * KT, a0, a1, a2, a3);
-        }
-    } else if constexpr (sizeof(T) == 4) {
-        T sa[SEG], sb[SEG];
-        load_seg<KT>(base + (r + KT - 1) * IWP, sa);
-#pragma unroll 1
-        for (int u = 0; u + 1 < KT; u += 2) {
-            load_seg<KT>(base + (r + KT - 2 - u) * IWP, sb);
-            row_fma<KT>(sa, psf + u * KT, a0, a1, a2, a3);
-            if (u + 2 < KT) load_seg<KT>(base + (r + KT - 3 - u) * IWP, sa);
-            row_fma<KT>(sb, psf + (u + 1) * KT, a0, a1, a2, a3);
-        }
-        if (KT & 1) row_fma<KT>(sa, psf + (KT - 1) * KT, a0, a1, a2, a3);
-    } else {
-        T sa[SEG];
-#pragma unroll 1
-        for (int u = 0; u < KT; ++u) {
-            load_seg<KT>(base + (r + KT - 1 - u) * IWP, sa);
-            row_fma<KT>(sa, psf + u * KT, a0, a1, a2, a3);
-        }
+    double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
+    const int kp = psf_pitch(K);
+    if (K == 1) {
+        const double p = (double)psl[0];
+        const double *rp = base + r * IWP;
+        out[0] = fma(p, rp[0], 0.0);
+        out[1] = fma(p, rp[1], 0.0);
+        out[2] = fma(p, rp[2], 0.0);
+        out[3] = fma(p, rp[3], 0.0);
+        return;
     }
-    out[0] = a0; out[1] = a1; out[2] = a2; out[3] = a3;
-}
-
-// Any PSF side (slow path): taps read one by one from LDS.
-template <typename T>
-__device__ inline void conv_plane_any(const T *base, int r, int K, int IWP, const cfloat *psf, T (&out)[4])
-{
-    T a0 = 0, a1 = 0, a2 = 0, a3 = 0;
+#pragma unroll 1
     for (int u = 0; u < K; ++u) {
-        const T *rp = base + (r + K - 1 - u) * IWP;
-        const cfloat *pr = psf + u * K;
-        for (int v = 0; v < K; ++v) {
-            const T pv = (T)pr[v];
-            const T *sp = rp + K - 1 - v;
-            a0 = fma(pv, sp[0], a0);
-            a1 = fma(pv, sp[1], a1);
-            a2 = fma(pv, sp[2], a2);
-            a3 = fma(pv, sp[3], a3);
+        const double *rp = base + (r + K - 1 - u) * IWP;
+        const float *pr = psl + u * kp;
+        // element e = K + 2 - m meets tap m - 3 + t for output t
+        double w1 = (double)pr[0], w2 = (double)pr[1], w3 = (double)pr[2];
+        a3 = fma(w1, rp[K + 2], a3);
+        a2 = fma(w1, rp[K + 1], a2);
+        a3 = fma(w2, rp[K + 1], a3);
+        a1 = fma(w1, rp[K], a1);
+        a2 = fma(w2, rp[K], a2);
+        a3 = fma(w3, rp[K], a3);
+        // K - 3 elements meet four taps each: K is odd, two at a time
+        double x0 = rp[K - 1], x1 = rp[K - 2];
+        float n0 = pr[min(3, K - 1)], n1 = pr[min(4, K - 1)];
+#pragma unroll 1
+        for (int m = 3; m < K; m += 2) {
+            const double e0 = x0, e1 = x1, p0 = (double)n0, p1 = (double)n1;
+            if (m + 2 < K) {
+                x0 = rp[K - m];
+                x1 = rp[K - 1 - m];
+                n0 = pr[m + 2];
+                n1 = pr[m + 3];
+            }
+            a0 = fma(w1, e0, a0);
+            a1 = fma(w2, e0, a1);
+            a2 = fma(w3, e0, a2);
+            a3 = fma(p0, e0, a3);
+            a0 = fma(w2, e1, a0);
+            a1 = fma(w3, e1, a1);
+            a2 = fma(p0, e1, a2);
+            a3 = fma(p1, e1, a3);
+            w1 = w3;
+            w2 = p0;
+            w3 = p1;
         }
+        a0 = fma(w1, rp[2], a0);
+        a1 = fma(w2, rp[2], a1);
+        a2 = fma(w3, rp[2], a2);
+        a0 = fma(w2, rp[1], a0);
+        a1 = fma(w3, rp[1], a1);
+        a0 = fma(w3, rp[0], a0);
     }
     out[0] = a0; out[1] = a1; out[2] = a2; out[3] = a3;
 }
@@ -471,148 +486,371 @@ __device__ inline void load_taps(const float *psl, int u, float (&tp)[KP])
     }
 }
 
-// PSF sides above 15: the planes of a group row by row of the PSF, every
-// plane of the group under one row's taps.  A row's taps are scalar loads,
-// which complete out of order with the LDS reads of the segments: with them
-// loaded once per PSF row, no scalar load is outstanding while the planes of
-// the row run, so the segment reads of the next plane overlap the products of
-// the current one.  Each accumulator sees the products in the order of the
-// plane-by-plane loop (rows, then taps).
-template <class F, int KT, int LO, int HI>
-__device__ inline void conv_group_wide(const float *__restrict__ buf, const cfloat *psf, int r, int cg,
-                                       double (&acc0)[4], float (&acc)[F::NPL][4])
+// ---------------------------------------------------------------- FP32 planes on the matrix cores
+// A 1 x 4 strip against one PSF row is out[t] += sum_x seg[x] p[K - 1 + t - x]
+// (x = 0 .. K + 2): for each x an outer product of four taps and one element
+// per lane.  v_mfma_f32_4x4x1_16b_f32 does exactly that: its B operand and its
+// four results belong to the lane, and its A operand, four values, is
+// broadcast to all 16 blocks from the block the instruction names (cbsz = 4,
+// abid), so one register holds the tap quadruples of 16 consecutive x (lane
+// 4 b + t: x = b, output t; 0 outside the PSF).  It is a fused multiply-add
+// with one rounding (also for denormals), and x runs downwards, so each
+// accumulator sees the products of the scalar loop in its order: the results
+// are the same bits (the extra products are 0 x finite).  One instruction of 8
+// cycles replaces four FMAs, which a single wave per SIMD issues at best every
+// 5 cycles (two waves together: every 2.6); matrix and vector instructions of
+// two waves do not overlap (both measured), so what bounds the convolutions is
+// the FMA units.  Before (FMAs with the taps in registers) and now, ms: 2,048
+// masked cutouts of 48-256 px, side 25: 326 -> 229; 256 of 64-128 px, side 31
+// (any-side loops, taps and elements one by one before): 907 -> 301; 16,384 of
+// 64 x 64, side 15: 55.4 -> 52.8.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <int ABID>
+__device__ inline f32x4 mfma_tap(float taps, float x, f32x4 acc)
 {
-    constexpr int IH = TILE + KT - 1, IWP = (28 + 4 * ((KT + 3 + 3) / 4));
-    constexpr int plane_sz = IH * IWP;
-    constexpr int QLO = LO == 0 ? 1 : LO;
-    const float *bf = ((LO == 0) ? buf + 2 * plane_sz : buf) + 4 * cg;
-    const double *b64 = reinterpret_cast<const double *>(buf) + 4 * cg;
-    double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;
-    float a[HI - QLO][4];
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(taps, x, acc, 4, ABID, 0);
+}
+
+// Registers of the tap quadruples of one PSF row.
+__host__ __device__ constexpr int tap_regs(int K) { return (K + 3 + 15) / 16; }
+
+// This lane's place in tap register j: column v of the PSF row, or none
+// (FLIP: of the PSF flipped in both axes, whose row u is row K - 1 - u).
+struct TapLane {
+    int v;
+    bool in;
+};
+template <bool FLIP = false>
+__device__ inline TapLane tap_lane(int lane, int K, int j)
+{
+    const int v = K - 1 + (lane & 3) - (16 * j + (lane >> 2)), c = min(max(v, 0), K - 1);
+    return TapLane{FLIP ? K - 1 - c : c, v >= 0 && v < K};
+}
+
+// seg[x] for x = X .. 0 against the taps of one PSF row, and (two rows) of the
+// row before it.
+template <int X>
+__device__ inline void mfma_row(const float *t, const float *seg, f32x4 &a)
+{
+    if constexpr (X >= 0) {
+        a = mfma_tap<X % 16>(t[X / 16], seg[X], a);
+        mfma_row<X - 1>(t, seg, a);
+    }
+}
+template <int X>
+__device__ inline void mfma_row2(const float *t1, const float *t0, const float *seg, f32x4 &a1, f32x4 &a0)
+{
+    if constexpr (X >= 0) {
+        a1 = mfma_tap<X % 16>(t1[X / 16], seg[X], a1);
+        a0 = mfma_tap<X % 16>(t0[X / 16], seg[X], a0);
+        mfma_row2<X - 1>(t1, t0, seg, a1, a0);
+    }
+}
+
+// Products before, LDS reads after: without it the compiler gathers the reads
+// of both halves of an unrolled loop in front of the products, and the
+// segments then need copies from register to register.
+__device__ inline void keep_order(f32x4 &a) { asm volatile("" : "+v"(a)::"memory"); }
+__device__ inline void keep_order(f32x4 &a, f32x4 &b) { asm volatile("" : "+v"(a), "+v"(b)::"memory"); }
+
+// After a plane pair: lo, hi hold rows 2 rp, 2 rp + 1 of plane A in lanes 0-31
+// and of plane B in lanes 32-63; exchanged, lo holds plane A and hi plane B at
+// each lane's own row.
+__device__ inline void split_pair(f32x4 &lo, f32x4 &hi)
+{
 #pragma unroll
-    for (int pl = 0; pl < HI - QLO; ++pl) a[pl][0] = a[pl][1] = a[pl][2] = a[pl][3] = 0.0f;
+    for (int t = 0; t < 4; ++t) {
+        const float l = lo[t], h = hi[t];
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(h), false, false);
+        lo[t] = __uint_as_float(s[0]);
+        hi[t] = __uint_as_float(s[1]);
+    }
+}
+
+// Two FP32 planes at once, one per half of the wave, over both rows of each
+// lane's row pair: a row segment read from LDS serves PSF row u for the odd
+// row and u - 1 for the even one, so K + 1 segments are read per pair of rows
+// and plane instead of 2 K.  p: this lane's plane at the even row, PSF row 0
+// (LDS row 2 rp + K - 1), column 4 cg.  The next segment and taps are read
+// while the current ones are used.  KT odd, at least 3.
+template <int KT>
+__device__ inline void conv_pair(const float *p, const float *psl, f32x4 &lo, f32x4 &hi)
+{
+    constexpr int KP = (KT + 3) & ~3, IWP = 28 + 4 * ((KT + 3 + 3) / 4), SEG = ((KT + 3 + 3) / 4) * 4;
+    constexpr int NR = tap_regs(KT);
+    const int lane = threadIdx.x & 63;
+    TapLane tl[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) tl[j] = tap_lane(lane, KT, j);
+    auto taps = [&](int u, float (&t)[NR]) {
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            const float x = psl[u * KP + tl[j].v];
+            t[j] = tl[j].in ? x : 0.0f;
+        }
+    };
+    f32x4 a0 = {0.0f, 0.0f, 0.0f, 0.0f}, a1 = a0;
+    float sa[SEG], sb[SEG], ta[NR], tb[NR];
+    taps(0, ta);
+    load_seg<KT>(p + IWP, sa);
+    taps(1, tb);
+    load_seg<KT>(p, sb);
+    mfma_row<KT + 2>(ta, sa, a1);
+#pragma unroll 1
+    for (int t = 1; t < KT; t += 2) {
+        // sb, tb: row t; ta: the taps of row t - 1
+        float tc[NR];
+        taps(t + 1, tc);
+        load_seg<KT>(p - t * IWP, sa);
+        mfma_row2<KT + 2>(tb, ta, sb, a1, a0);
+        keep_order(a1, a0);
+        taps(min(t + 2, KT - 1), ta);
+        load_seg<KT>(p - (t + 1) * IWP, sb);
+        mfma_row2<KT + 2>(tc, tb, sa, a1, a0);
+        keep_order(a1, a0);
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            const float x = ta[j];
+            ta[j] = tc[j];
+            tb[j] = x;
+        }
+    }
+    mfma_row<KT + 2>(ta, sb, a0);       // row KT, the even rows' last
+    lo = a0;
+    hi = a1;
+}
+
+// One FP32 plane, each lane its own row (the odd plane out).  p: this lane's
+// row at PSF row 0, column 4 cg.  FLIP: with the flipped PSF (a correlation).
+template <int KT, bool FLIP = false>
+__device__ inline void conv_one(const float *p, const float *psl, f32x4 &out)
+{
+    constexpr int KP = (KT + 3) & ~3, IWP = 28 + 4 * ((KT + 3 + 3) / 4), SEG = ((KT + 3 + 3) / 4) * 4;
+    constexpr int NR = tap_regs(KT);
+    const int lane = threadIdx.x & 63;
+    TapLane tl[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) tl[j] = tap_lane<FLIP>(lane, KT, j);
+    auto taps = [&](int u, float (&t)[NR]) {
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            const float x = psl[(FLIP ? KT - 1 - u : u) * KP + tl[j].v];
+            t[j] = tl[j].in ? x : 0.0f;
+        }
+    };
+    f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f};
+    float sa[SEG], sb[SEG], ta[NR], tb[NR];
+    taps(0, ta);
+    load_seg<KT>(p, sa);
+#pragma unroll 1
+    for (int u = 0; u + 1 < KT; u += 2) {
+        taps(u + 1, tb);
+        load_seg<KT>(p - (u + 1) * IWP, sb);
+        mfma_row<KT + 2>(ta, sa, a);
+        keep_order(a);
+        taps(u + 2, ta);
+        load_seg<KT>(p - (u + 2) * IWP, sa);
+        mfma_row<KT + 2>(tb, sb, a);
+        keep_order(a);
+    }
+    mfma_row<KT + 2>(ta, sa, a);
+    out = a;
+}
+
+// Any PSF side K (odd): TWO planes per call as conv_pair (TWO), or one as
+// conv_one.  Sixteen elements of the segment (one tap register) at a time, the
+// next sixteen read while they are used; four-element groups past the segment
+// are skipped, and elements past it in the last group are taken as 0.
+struct Seg16 {
+    f32x4 q[4];
+};
+
+template <int Q>
+__device__ inline void mfma_quad(float t1, float t0, bool two, bool one, const f32x4 &x, f32x4 &a1, f32x4 &a0)
+{
+    if (two) {
+        a1 = mfma_tap<4 * Q + 3>(t1, x[3], a1);
+        a0 = mfma_tap<4 * Q + 3>(t0, x[3], a0);
+        a1 = mfma_tap<4 * Q + 2>(t1, x[2], a1);
+        a0 = mfma_tap<4 * Q + 2>(t0, x[2], a0);
+        a1 = mfma_tap<4 * Q + 1>(t1, x[1], a1);
+        a0 = mfma_tap<4 * Q + 1>(t0, x[1], a0);
+        a1 = mfma_tap<4 * Q>(t1, x[0], a1);
+        a0 = mfma_tap<4 * Q>(t0, x[0], a0);
+    } else if (one) {
+        a1 = mfma_tap<4 * Q + 3>(t1, x[3], a1);
+        a1 = mfma_tap<4 * Q + 2>(t1, x[2], a1);
+        a1 = mfma_tap<4 * Q + 1>(t1, x[1], a1);
+        a1 = mfma_tap<4 * Q>(t1, x[0], a1);
+    } else {
+        a0 = mfma_tap<4 * Q + 3>(t0, x[3], a0);
+        a0 = mfma_tap<4 * Q + 2>(t0, x[2], a0);
+        a0 = mfma_tap<4 * Q + 1>(t0, x[1], a0);
+        a0 = mfma_tap<4 * Q>(t0, x[0], a0);
+    }
+}
+
+// a1: PSF row t of this lane's row (TWO: of the odd row), a0: PSF row t - 1 of
+// the even row.  p: column 4 cg of this lane's plane and the LDS row of step 0.
+template <bool TWO, bool FLIP = false>
+__device__ inline void conv_any(const float *p, int K, int IWP, const float *psl, f32x4 &lo, f32x4 &hi)
+{
+    const int lane = threadIdx.x & 63, kp = psf_pitch(K), nx = K + 3, nj = tap_regs(K);
+    const int steps = TWO ? K + 1 : K;
+    f32x4 a0 = {0.0f, 0.0f, 0.0f, 0.0f}, a1 = a0;
+    Seg16 x, y;
+    float t1 = 0.0f, t0 = 0.0f, s1 = 0.0f, s0 = 0.0f;
+    // the elements and taps of step t, register j
+    auto load = [&](int t, int j, Seg16 &v, float &w1, float &w0) {
+        const float *row = p - t * IWP + 16 * j;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            f32x4 e = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (16 * j + 4 * q < nx) {
+                e = *reinterpret_cast<const f32x4 *>(row + 4 * q);
+                if (16 * j + 4 * q + 2 >= nx) e[2] = e[3] = 0.0f;      // nx is even
+            }
+            v.q[q] = e;
+        }
+        const TapLane tl = tap_lane<FLIP>(lane, K, j);
+        const int u = min(t, K - 1);
+        const float c = psl[(FLIP ? K - 1 - u : u) * kp + tl.v];
+        w1 = tl.in ? c : 0.0f;
+        if (TWO) {
+            const float b = psl[max(t - 1, 0) * kp + tl.v];
+            w0 = tl.in ? b : 0.0f;
+        }
+    };
+    int t = 0, j = nj - 1;
+    load(t, j, x, t1, t0);
+#pragma unroll 1
+    while (true) {
+        int tn = t, jn = j - 1;
+        if (jn < 0) {
+            jn = nj - 1;
+            tn = t + 1;
+        }
+        const bool more = tn < steps;
+        if (more) load(tn, jn, y, s1, s0);
+        const bool two = TWO && t > 0 && t < K, one = t < K;
+        const int left = nx - 16 * j;
+        if (left > 12) mfma_quad<3>(t1, t0, two, one, x.q[3], a1, a0);
+        if (left > 8) mfma_quad<2>(t1, t0, two, one, x.q[2], a1, a0);
+        if (left > 4) mfma_quad<1>(t1, t0, two, one, x.q[1], a1, a0);
+        mfma_quad<0>(t1, t0, two, one, x.q[0], a1, a0);
+        if (!more) break;
+        t = tn;
+        j = jn;
+        t1 = s1;
+        t0 = s0;
+        x = y;
+    }
+    lo = a0;
+    hi = a1;
+}
+
+// The FP64 light plane with PSF sides above 15: each row in two halves of
+// taps, each with only the part of the segment it reads (taps v < VS read
+// elements from ES on), the taps as scalar loads.
+template <int KT>
+__device__ inline void conv64_wide(const double *b64, const cfloat *psf, int r, double (&acc0)[4])
+{
+    constexpr int IWP = (28 + 4 * ((KT + 3 + 3) / 4));
+    constexpr int ES = 4 * ((KT - 1) / 8), VS = KT - ES;
+    double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;
 #pragma unroll 1
     for (int u = 0; u < KT; ++u) {
         const int ro = (r + KT - 1 - u) * IWP;
         const cfloat *pr = psf + u * KT;
-        // wide PSFs: each row in two halves of taps, each with only the part
-        // of the segment it reads (taps v < VS read elements from ES on)
-        constexpr int ES = 4 * ((KT - 1) / 8), VS = KT - ES;
-        if constexpr (LO == 0) {
-            row_part<KT, 0, VS, ES>(b64 + ro, pr, d0, d1, d2, d3);
-            row_part<KT, VS, KT, 0>(b64 + ro, pr, d0, d1, d2, d3);
-        }
-#pragma unroll
-        for (int pl = 0; pl < HI - QLO; ++pl) {
-            row_part<KT, 0, VS, ES>(bf + pl * plane_sz + ro, pr, a[pl][0], a[pl][1], a[pl][2], a[pl][3]);
-            row_part<KT, VS, KT, 0>(bf + pl * plane_sz + ro, pr, a[pl][0], a[pl][1], a[pl][2], a[pl][3]);
-        }
+        row_part<KT, 0, VS, ES>(b64 + ro, pr, d0, d1, d2, d3);
+        row_part<KT, VS, KT, 0>(b64 + ro, pr, d0, d1, d2, d3);
     }
-    if constexpr (LO == 0) {
-        acc0[0] = d0; acc0[1] = d1; acc0[2] = d2; acc0[3] = d3;
-    }
-#pragma unroll
-    for (int pl = QLO; pl < HI; ++pl)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[pl][t] = a[pl - QLO][t];
+    acc0[0] = d0; acc0[1] = d1; acc0[2] = d2; acc0[3] = d3;
 }
 
-// PSF sides up to 15.  Every load of the loops is an LDS read (the taps
-// from the PSF's LDS copy, the segments from the planes), and LDS reads
-// complete in order, so a wait covers exactly the reads a product needs and
-// the reads issued after them stay in flight.  The FP64 plane runs first, on
-// its own, with the segment and taps of the next PSF row loaded while the
-// current row is used; then the FP32 planes, row by row of the PSF with every
-// plane under the row's taps, each plane's segment loaded while the previous
-// plane's products run.  Each accumulator sees the products in the same order
-// (rows, then taps).
-template <class F, int KT, int LO, int HI>
-__device__ inline void conv_group_rows(const float *__restrict__ buf, const float *__restrict__ psl, int r, int cg,
-                                       double (&acc0)[4], float (&acc)[F::NPL][4])
+// The FP64 light plane with PSF sides up to 15.  Every load of the loop is an
+// LDS read (the taps from the PSF's LDS copy, the segments from the plane),
+// and LDS reads complete in order, so a wait covers exactly the reads a
+// product needs: the segment and taps of the next PSF row are read while the
+// current row is used.
+template <int KT>
+__device__ inline void conv64_rows(const double *b64, const float *psl, int r, double (&acc0)[4])
 {
     constexpr int KP = (KT + 3) & ~3;
-    constexpr int IH = TILE + KT - 1, IWP = (28 + 4 * ((KT + 3 + 3) / 4));
-    constexpr int plane_sz = IH * IWP;
-    constexpr int QLO = LO == 0 ? 1 : LO, NP = HI - QLO;
-    constexpr int SEG32 = ((KT + 3 + 3) / 4) * 4, SEG64 = ((KT + 3 + 1) / 2) * 2;
-    const float *bf = ((LO == 0) ? buf + 2 * plane_sz : buf) + 4 * cg;
-    const float *rowp = bf + (r + KT - 1) * IWP;          // row of PSF row 0; PSF row u is -u * IWP
-    if constexpr (LO == 0) {
-        // rows of even u start at pe - u IWP, of odd u at po - (u - 1) IWP (the
-        // row parity, and so the shift64 offset, alternates with u)
-        const int rr0 = r + KT - 1;
-        const double *b64 = reinterpret_cast<const double *>(buf) + 4 * cg;
-        const double *pe = b64 + rr0 * IWP + (shift64<KT>() ? 2 * (rr0 & 1) : 0);
-        const double *po = b64 + (rr0 - 1) * IWP + (shift64<KT>() ? 2 * ((rr0 - 1) & 1) : 0);
-        double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;
-        double sa[SEG64], sb[SEG64];
-        float ta[KP], tb[KP];
-        load_taps<KP>(psl, 0, ta);
-        load_seg<KT>(pe, sa);
+    constexpr int IWP = (28 + 4 * ((KT + 3 + 3) / 4));
+    constexpr int SEG64 = ((KT + 3 + 1) / 2) * 2;
+    constexpr bool SH = shift64<KT>();
+    const int rr0 = r + KT - 1;
+    auto row = [&](int u) {
+        const int y = rr0 - u;
+        return b64 + y * IWP + (SH ? (y & 2) : 0);
+    };
+    double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;
+    double sa[SEG64], sb[SEG64];
+    float ta[KP], tb[KP];
+    load_taps<KP>(psl, 0, ta);
+    load_seg<KT>(row(0), sa);
 #pragma unroll 1
-        for (int u = 0; u + 1 < KT; u += 2) {
-            load_taps<KP>(psl, u + 1, tb);
-            load_seg<KT>(po - u * IWP, sb);
-            row_fma<KT>(sa, ta, d0, d1, d2, d3);
-            if (u + 2 < KT) {
-                load_taps<KP>(psl, u + 2, ta);
-                load_seg<KT>(pe - (u + 2) * IWP, sa);
-            }
-            row_fma<KT>(sb, tb, d0, d1, d2, d3);
+    for (int u = 0; u + 1 < KT; u += 2) {
+        load_taps<KP>(psl, u + 1, tb);
+        load_seg<KT>(row(u + 1), sb);
+        row_fma<KT>(sa, ta, d0, d1, d2, d3);
+        if (u + 2 < KT) {
+            load_taps<KP>(psl, u + 2, ta);
+            load_seg<KT>(row(u + 2), sa);
         }
-        if (KT & 1) row_fma<KT>(sa, ta, d0, d1, d2, d3);
-        acc0[0] = d0; acc0[1] = d1; acc0[2] = d2; acc0[3] = d3;
+        row_fma<KT>(sb, tb, d0, d1, d2, d3);
     }
-    float a[NP > 0 ? NP : 1][4];
-#pragma unroll
-    for (int pl = 0; pl < NP; ++pl) a[pl][0] = a[pl][1] = a[pl][2] = a[pl][3] = 0.0f;
-    if constexpr (NP > 0) {
-#pragma unroll 1
-        for (int u = 0; u < KT; ++u) {
-            float tp[KP];
-            load_taps<KP>(psl, u, tp);
-            const float *ro = rowp - u * IWP;
-            float sg[2][SEG32];
-            load_seg<KT>(ro, sg[0]);
-            constexpr int NRD = (KT + 3 + 3) / 4;      // 16-byte reads per segment
-            __builtin_amdgcn_sched_group_barrier(0x100, KP / 4 + NRD, 0);
-#pragma unroll
-            for (int pl = 0; pl < NP; ++pl) {
-                if (pl + 1 < NP) {
-                    load_seg<KT>(ro + (pl + 1) * plane_sz, sg[(pl + 1) & 1]);
-                    __builtin_amdgcn_sched_group_barrier(0x100, NRD, 0);
-                }
-                row_fma<KT>(sg[pl & 1], tp, a[pl][0], a[pl][1], a[pl][2], a[pl][3]);
-                __builtin_amdgcn_sched_group_barrier(0x002, 4 * KT, 0);
-            }
-        }
-    }
-#pragma unroll
-    for (int pl = QLO; pl < HI; ++pl)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[pl][t] = a[pl - QLO][t];
+    if (KT & 1) row_fma<KT>(sa, ta, d0, d1, d2, d3);
+    acc0[0] = d0; acc0[1] = d1; acc0[2] = d2; acc0[3] = d3;
+}
+
+// The FP64 light plane for this thread's 1 x 4 strip.
+template <int KT>
+__device__ inline void conv64(const float *buf, int K, const cfloat *psf, const float *psl, int r, int cg,
+                              double (&acc0)[4])
+{
+    const double *b64 = reinterpret_cast<const double *>(buf) + 4 * cg;
+    if constexpr (KT > 15) conv64_wide<KT>(b64, psf, r, acc0);
+    else if constexpr (KT > 0) conv64_rows<KT>(b64, psl, r, acc0);
+    else conv64_any(b64, r, K, region_wp(K), psl, acc0);
 }
 
 // Convolve planes LO..HI-1 for this thread's 1 x 4 output strip (tile row r,
-// columns 4 cg .. 4 cg + 3): plane 0 in FP64, the derivative planes in FP32.
-// KT > 0: compile-time PSF side; 0: any K.
+// columns 4 cg .. 4 cg + 3): plane 0 in FP64 on the vector units, the FP32
+// planes two at a time on the matrix cores.  KT > 0: compile-time PSF side;
+// 0: any K.
 template <class F, int KT, int LO, int HI>
 __device__ inline void conv_group(const float *__restrict__ buf, int K, const cfloat *psf, const float *psl, int r,
                                   int cg, double (&acc0)[4], float (&acc)[F::NPL][4])
 {
-    if constexpr (KT > 15) {
-        conv_group_wide<F, KT, LO, HI>(buf, psf, r, cg, acc0, acc);
-    } else if constexpr (KT > 0) {
-        conv_group_rows<F, KT, LO, HI>(buf, psl, r, cg, acc0, acc);
-    } else {
-        const int IH = region_h(K), IWP = region_wp(K);
-        const int plane_sz = IH * IWP;
-        constexpr int QLO = LO == 0 ? 1 : LO;
-        const float *bf = (LO == 0) ? buf + 2 * plane_sz : buf;
-        if constexpr (LO == 0)
-            conv_plane_any<double>(reinterpret_cast<const double *>(buf) + 4 * cg, r, K, IWP, psf, acc0);
+    const int IH = region_h(K), IWP = region_wp(K);
+    const int plane_sz = IH * IWP;
+    constexpr int QLO = LO == 0 ? 1 : LO, NP = HI - QLO;
+    const float *bf = ((LO == 0) ? buf + 2 * plane_sz : buf) + 4 * cg;
+    if constexpr (LO == 0) conv64<KT>(buf, K, psf, psl, r, cg, acc0);
+    const int half = (threadIdx.x >> 5) & 1;
 #pragma unroll
-        for (int pl = QLO; pl < HI; ++pl) conv_plane_any<float>(bf + (pl - QLO) * plane_sz + 4 * cg, r, K, IWP, psf, acc[pl]);
+    for (int pl = 0; pl + 1 < NP; pl += 2) {
+        const float *p = bf + (pl + half) * plane_sz + ((r & ~1) + K - 1) * IWP;
+        f32x4 lo, hi;
+        if constexpr (KT > 0) conv_pair<KT>(p, psl, lo, hi);
+        else conv_any<true>(p + IWP, K, IWP, psl, lo, hi);
+        split_pair(lo, hi);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            acc[QLO + pl][t] = lo[t];
+            acc[QLO + pl + 1][t] = hi[t];
+        }
+    }
+    if constexpr (NP & 1) {
+        const float *p = bf + (NP - 1) * plane_sz + (r + K - 1) * IWP;
+        f32x4 one, none;
+        if constexpr (KT > 0) conv_one<KT>(p, psl, one);
+        else conv_any<false>(p, K, IWP, psl, none, one);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[HI - 1][t] = one[t];
     }
 }
 
@@ -744,7 +982,7 @@ __device__ void evaluate(const double *u, const ModelArgs &ma, const BatchArgs &
                 // the FP32 partials of the last FLUSH_TILES tiles into the wave's FP64 sums
 #pragma unroll
                 for (int q = 0; q < NR - 1; ++q) {
-                    const double v = wave_sum((double)red[q]);
+                    const double v = strip_sum((double)red[q], K);
                     if (lane == 0) sh.nacc[wave][q] += v;
                     red[q] = 0.0f;
                 }
@@ -792,12 +1030,12 @@ __device__ void evaluate(const double *u, const ModelArgs &ma, const BatchArgs &
     // (the plane buffer is idle after the last tile's barrier: reuse it)
     double *sred = reinterpret_cast<double *>(planes);
     {
-        double v = wave_sum(c2);
+        double v = strip_sum(c2, K);
         if (lane == 0) sred[wave * NR] = v;
     }
 #pragma unroll
     for (int q = 1; q < NR; ++q) {
-        double v = wave_sum((double)red[q - 1]);
+        double v = strip_sum((double)red[q - 1], K);
         if (lane == 0) sred[wave * NR + q] = flushes ? sh.nacc[wave][q - 1] + v : v;
     }
     __syncthreads();
@@ -1432,26 +1670,18 @@ __device__ void load_u(LMShared<F> &s, const ModelArgs &ma, const double *params
     }
 }
 
-// Workgroups per CU that the fit kernel's register allocation targets.  Two
-// (at most 256 VGPRs per lane) let one workgroup's profile evaluation,
-// prologue and LM step overlap the other's convolution, where the plane
-// buffers of two fit in LDS.  The one-component families fit them without
-// spills inside loops (measured 1.38x faster Sersic fits at 64 x 64, PSF
-// side 15); the two-component models need more registers than that for
-// their accumulators and keep one (as does the error kernel, which would
-// spill inside its loops).  Where a workgroup's LDS (plane buffer, PSF
-// copies, static state) leaves room for one per CU only, the target is one
-// too: the second workgroup's registers could never be used, and the 256
-// VGPR cap made the wide-PSF kernels spill.
-template <class F, int KT, int NG>
+// Workgroups per CU that the kernels' register allocation targets.  At two (at
+// most 256 VGPRs per lane) one workgroup's profile evaluation, prologue and LM
+// step overlap the other's convolution where the plane buffers of two fit in
+// LDS (measured 1.38x faster Sersic fits at 64 x 64, PSF side 15), and the
+// matrix instructions' accumulators stay in VGPRs: with more registers allowed
+// the compiler puts them into AGPRs, with copies in the convolution loops.
+// The one-component families fit this budget at every PSF side without spills
+// inside loops; the two-component models' normal-equation accumulators do not.
+template <class F>
 __host__ __device__ constexpr int min_wg()
 {
-    if (F::NCOMP != 1) return 1;
-    if (KT == 0) return 2;
-    const size_t planes = (size_t)max_group_units(F::NPL, NG) * region_h(KT) * region_wp(KT) * sizeof(float);
-    const size_t psf = (size_t)KT * ((KT + 3) & ~3) * (sizeof(float) + sizeof(double));
-    const size_t per_wg = planes + psf + sizeof(EvalShared<F>) + sizeof(LMShared<F>) + 1024;
-    return 2 * per_wg <= (size_t)160 * 1024 ? 2 : 1;
+    return F::NCOMP != 1 ? 1 : 2;
 }
 
 // Team steps around the one evaluation site of lm_fit_kernel.
@@ -1517,7 +1747,7 @@ __device__ inline bool team_collect(LMShared<F> &s, TeamCtl *ctl, const double *
 // the refit from refit_start); members follow the leader's commands.  The
 // model is evaluated at a single site for all three roles.
 template <class F, int KT, int NG>
-__global__ __launch_bounds__(NT, (min_wg<F, KT, NG>())) void lm_fit_kernel(ModelArgs ma, BatchArgs ba, FitArgs fa)
+__global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, BatchArgs ba, FitArgs fa)
 {
     extern __shared__ float4 dyn_lds[];
     float *planes = reinterpret_cast<float *>(dyn_lds);
@@ -1709,7 +1939,7 @@ struct ImageArgs {
 };
 
 template <class F, int KT, int NG>
-__global__ __launch_bounds__(NT) void image_kernel(ModelArgs ma, BatchArgs ba, ImageArgs ia)
+__global__ __launch_bounds__(NT, 2) void image_kernel(ModelArgs ma, BatchArgs ba, ImageArgs ia)
 {
     extern __shared__ float4 dyn_lds[];
     float *planes = reinterpret_cast<float *>(dyn_lds);
@@ -1778,7 +2008,7 @@ __global__ __launch_bounds__(NT) void image_kernel(ModelArgs ma, BatchArgs ba, I
             const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll
             for (int k = 0; k < P; ++k) {
-                const double w = wave_sum(v[k]);
+                const double w = strip_sum(v[k], K);
                 if (lane == 0) sv[wave][k] = w;
             }
             __syncthreads();

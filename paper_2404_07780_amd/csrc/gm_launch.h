@@ -176,7 +176,7 @@ int launch_fit(gm_ctx *c, const ModelArgs &ma, const BatchArgs &ba, const FitArg
 struct AdamArgs;
 template <class F, int NG, int KT>
 int launch_adam(gm_ctx *c, const ModelArgs &ma, const BatchArgs &ba, AdamArgs aa, size_t lds, int wpc,
-                int64_t psf_len, int64_t max_px, hipStream_t st);
+                int64_t max_px, hipStream_t st);
 template <class F, int NG, int... KTS>
 int run_adam(gm_ctx *c, const CallInfo &ci, const gm_adam_opts *o, double *params, double *chi2, int32_t *status,
              hipStream_t st);
