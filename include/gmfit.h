@@ -156,7 +156,9 @@ int gm_jacobian(gm_ctx *ctx, const gm_model *model, const gm_batch *batch,
  *     method).  0 = automatic: when a launch has fewer fits than resident
  *     workgroups, each fit gets min(32, resident / fits, its tiles); 1 = one
  *     workgroup per fit; k > 1 = min(k, tiles) workgroups for every fit of at
- *     least team_min_tiles 32 x 32 tiles, one for the others;
+ *     least team_min_tiles 32 x 32 tiles, one for the others.  Except at 1,
+ *     workgroups of a launch without teams that have run out of fits make
+ *     tiles for the fits still running (results the same bits);
  *   team_min_tiles -- see team (0 = 1);
  *   team_wait_us -- bound of every wait between the workgroups of a team, in
  *     microseconds (0 = 20 s); a fit whose team passes it ends with

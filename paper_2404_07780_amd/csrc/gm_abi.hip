@@ -154,6 +154,22 @@ int ensure_team(gm_ctx *c, size_t bytes, void **out)
     return GM_OK;
 }
 
+int ensure_help(gm_ctx *c, size_t bytes, void **out)
+{
+    if (c->help_bytes < bytes) {
+        if (c->help) {
+            if (hipDeviceSynchronize() != hipSuccess) return GM_EHIP;
+            (void)hipFree(c->help);
+            c->help = nullptr;
+            c->help_bytes = 0;
+        }
+        if (hipMalloc(&c->help, bytes) != hipSuccess) return GM_ENOMEM;
+        c->help_bytes = bytes;
+    }
+    *out = c->help;
+    return GM_OK;
+}
+
 int stage(gm_ctx *c, const CallInfo &ci, const void *extra, size_t extra_bytes, hipStream_t st, Staged *out)
 {
     const gm_batch *b = ci.b;
@@ -248,11 +264,12 @@ void ctx_release(gm_ctx *c)
     if (c->mlp_ws) (void)hipFree(c->mlp_ws);
     if (c->aux) (void)hipFree(c->aux);
     if (c->team) (void)hipFree(c->team);
+    if (c->help) (void)hipFree(c->help);
     if (c->staged) (void)hipEventDestroy(c->staged);
-    c->dev = c->host = c->mlp_ws = c->aux = c->team = nullptr;
+    c->dev = c->host = c->mlp_ws = c->aux = c->team = c->help = nullptr;
     c->unit_psf = nullptr;
     c->staged = nullptr;
-    c->dev_bytes = c->host_bytes = c->mlp_ws_bytes = c->aux_bytes = c->team_bytes = 0;
+    c->dev_bytes = c->host_bytes = c->mlp_ws_bytes = c->aux_bytes = c->team_bytes = c->help_bytes = 0;
 }
 
 namespace {

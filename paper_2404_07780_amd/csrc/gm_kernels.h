@@ -940,6 +940,262 @@ __device__ inline void boot_weights(const BootArgs &bt, int64_t pix0, float (&m)
     for (int t = 0; t < 4; ++t) m[t] = (float)poisson1(w[off + t]);
 }
 
+// ---------------------------------------------------------------- helpers
+// A fit that needs many trials (up to 100, against ten for most) or has many
+// tiles outlives the rest of its launch: 2,048 cutouts of 48-256 px on 256
+// workgroups kept one workgroup busy for 220 ms, the others for 82 on
+// average.  A workgroup that finds the queue empty therefore helps the fits
+// still running, tile by tile: it takes the next tile of an evaluation, makes
+// its convolved planes and leaves them in memory; the fit's own workgroup (the
+// owner) takes tiles too and adds the products of all of them itself, in tile
+// order, so a thread's FP32 sums see the same values in the same order and the
+// results are the same bits with any number of helpers.
+//
+// An owner that sees idle workgroups claims one of kHelpSlots slots for the
+// rest of its fit.  Per evaluation it writes the prologue's result (scalars
+// and window tables) into the slot and opens a ticket {epoch, tiles, next};
+// who adds one to `next` has that tile.  A tile's planes go to entry
+// tile % kHelpRing of the slot, marked with help_seq(epoch, tile); the owner
+// frees entries by advancing `added`.  The tile the owner waits for is held by
+// a running workgroup, whose entry is free, so every wait ends; each is bounded
+// by spin_limit all the same: past it the owner makes the tile itself and
+// leaves the slot for good (a late helper can then only write to that slot),
+// and a helper that finds nothing to do for that long ends.
+// The board is zeroed before every launch; slots past n_slots are never used.
+constexpr int kHelpSlots = 64;
+constexpr int kHelpRing = 16;
+
+struct HelpSlot {
+    int owner;                    // 1: claimed
+    int epoch;                    // of the last evaluation shared
+    int src;                      // galaxy
+    int added;                    // tiles of this evaluation the owner has added
+    int seq[kHelpRing];
+    int pad[12];
+};
+struct HelpBoard {
+    int idle;                     // workgroups that have turned helpers
+    int done;                     // queue entries finished
+    int pad[14];
+    unsigned long long ticket[kHelpSlots];      // epoch << 32 | tiles << 16 | next
+    HelpSlot slot[kHelpSlots];
+};
+
+enum { HELP_NONE = 0, HELP_OWNER, HELP_HELPER };
+enum { TILE_SUM = 0, TILE_STORE, TILE_LOAD };     // make + add, make + leave in memory, read + add
+
+// A workgroup's part in a shared evaluation (wave-uniform).
+struct HelpState {
+    HelpBoard *board = nullptr;
+    char *base = nullptr;         // the slots' memory
+    int64_t stride = 0, limit = 0;
+    int n_slots = 0, n_entries = 0;
+    int role = HELP_NONE;
+    int slot = -1;
+    int epoch = 0;
+    int tile = 0;                 // HELP_HELPER: the tile it took
+    __device__ char *buf() const { return base + slot * stride; }
+};
+
+template <typename T>
+__device__ inline T agent_load(const T *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline void agent_store(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// This wave's stores have reached the memory that all dies see (agent-scope
+// stores write through).  What helpers and owners hand over is written and
+// read by agent-scope accesses alone, stores_done and a barrier before the
+// mark that publishes it: no release or acquire, whose L2 write-back and
+// invalidation would hit every workgroup of the die (with them, 2,048 fits of
+// 64 x 64 ran 12% slower helped than alone).
+__device__ inline void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ inline int help_seq(int epoch, int tile) { return (epoch << 11) | (tile + 1); }
+__device__ inline unsigned long long help_take(unsigned long long *ticket)
+{
+    return __hip_atomic_fetch_add(ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The part of EvalShared that the prologue fills (all but nacc).
+template <class F>
+__host__ __device__ constexpr size_t help_head_bytes()
+{
+    return sizeof(EvalShared<F>) - sizeof(double) * NWAVE * (F::P + F::P * (F::P + 1) / 2);
+}
+// Bytes of one ring entry (a tile's planes) and of one slot's memory.
+template <class F>
+__host__ __device__ constexpr size_t help_entry_bytes()
+{
+    return (size_t)NT * (4 * sizeof(double) + (F::NPL - 1) * 4 * sizeof(float));
+}
+template <class F>
+__host__ __device__ constexpr size_t help_slot_bytes()
+{
+    return ((help_head_bytes<F>() + 255) & ~(size_t)255) + kHelpRing * help_entry_bytes<F>();
+}
+
+// One strip's values to or from a ring entry, as 8-byte words of coalesced
+// agent-scope accesses (they reach the memory that all dies see).
+template <class F, bool STORE>
+__device__ inline void help_strip(char *buf, int tile, double (&acc0)[4], float (&acc)[F::NPL][4])
+{
+    unsigned long long *e = reinterpret_cast<unsigned long long *>(
+        buf + ((help_head_bytes<F>() + 255) & ~(size_t)255) + (size_t)(tile % kHelpRing) * help_entry_bytes<F>());
+    e += threadIdx.x;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        if (STORE) agent_store(e + t * NT, __builtin_bit_cast(unsigned long long, acc0[t]));
+        else acc0[t] = __builtin_bit_cast(double, agent_load(e + t * NT));
+    }
+    e += 4 * NT;
+#pragma unroll
+    for (int q = 1; q < F::NPL; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            unsigned long long *w = e + (2 * (q - 1) + h) * NT;
+            if (STORE) {
+                agent_store(w, (unsigned long long)__float_as_uint(acc[q][2 * h]) |
+                                   ((unsigned long long)__float_as_uint(acc[q][2 * h + 1]) << 32));
+            } else {
+                const unsigned long long v = agent_load(w);
+                acc[q][2 * h] = __uint_as_float((unsigned)v);
+                acc[q][2 * h + 1] = __uint_as_float((unsigned)(v >> 32));
+            }
+        }
+}
+
+// All threads: this workgroup's agent-scope stores so far, then *p = v.
+template <typename T>
+__device__ inline void help_publish(T *p, T v)
+{
+    stores_done();
+    __syncthreads();
+    if (threadIdx.x == 0) agent_store(p, v);
+}
+
+// Owner, all threads: a slot for this fit (kept until help_release).
+template <class F>
+__device__ inline bool help_claim(HelpState &hp, int *sh_help)
+{
+    if (hp.slot >= 0) return true;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int got = -1;
+        for (int i = 0; i < 8 && got < 0; ++i) {
+            const int k = (int)((blockIdx.x + 23 * i) % (unsigned)hp.n_slots);
+            int free_ = 0;
+            if (__hip_atomic_compare_exchange_strong(&hp.board->slot[k].owner, &free_, 1, __ATOMIC_RELAXED,
+                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                got = k;
+        }
+        sh_help[0] = got;
+        sh_help[1] = got >= 0 ? agent_load(&hp.board->slot[got].epoch) : 0;
+    }
+    __syncthreads();
+    hp.slot = uniform(sh_help[0]);
+    hp.epoch = uniform(sh_help[1]);
+    return hp.slot >= 0;
+}
+
+// Owner, all threads, after the prologue: opens the evaluation's tickets.
+template <class F>
+__device__ inline void help_open(const EvalShared<F> &sh, HelpState &hp, int src, int ntiles)
+{
+    HelpSlot *hs = hp.board->slot + hp.slot;
+    ++hp.epoch;
+    unsigned long long *d = reinterpret_cast<unsigned long long *>(hp.buf());
+    const unsigned long long *e = reinterpret_cast<const unsigned long long *>(&sh);
+    for (int i = threadIdx.x; i < (int)(help_head_bytes<F>() / 8); i += NT) agent_store(d + i, e[i]);
+    if (threadIdx.x == 0) {
+        agent_store(&hs->src, src);
+        agent_store(&hs->epoch, hp.epoch);
+        agent_store(&hs->added, 0);
+    }
+    help_publish(hp.board->ticket + hp.slot,
+                 ((unsigned long long)(unsigned)hp.epoch << 32) | ((unsigned long long)ntiles << 16));
+}
+
+// Owner, thread 0: what to do for tile `next`, the first not yet added: add it
+// from the ring (TILE_LOAD), make and add it (TILE_SUM), or make a later tile
+// for the ring (TILE_STORE).  held: a tile taken while the ring had no room
+// for it (-1: none); drained: no tiles left to take.
+__device__ inline int help_next(HelpState &hp, int next, int ntiles, int &held, int &drained, int &tile, int &lost)
+{
+    HelpSlot *hs = hp.board->slot + hp.slot;
+    agent_store(&hs->added, next);
+    const int *mark = hs->seq + next % kHelpRing;
+    const int want = help_seq(hp.epoch, next);
+    tile = next;
+    if (lost) return TILE_SUM;
+    if (agent_load(mark) == want) return TILE_LOAD;
+    if (held < 0 && !drained) {
+        const int t = (int)(help_take(hp.board->ticket + hp.slot) & 0xffff);
+        if (t < ntiles) held = t;
+        else drained = 1;
+    }
+    if (held >= 0 && held < next + kHelpRing) {
+        tile = held;
+        held = -1;
+        return tile == next ? TILE_SUM : TILE_STORE;
+    }
+    const int64_t t0 = wall_clock64();
+    while (agent_load(mark) != want) {
+        if (wall_clock64() - t0 > hp.limit) {
+            lost = 1;
+            agent_store(hp.board->ticket + hp.slot, 0ull);
+            return TILE_SUM;
+        }
+        __builtin_amdgcn_s_sleep(2);
+    }
+    return TILE_LOAD;
+}
+
+// Helper, wave 0: takes a tile of some open evaluation into hp; false when
+// every fit has ended, or nothing was found for the limit's time.
+__device__ inline bool help_find(HelpState &hp, int n_entries)
+{
+    static_assert(kHelpSlots == 64, "one lane per slot");
+    HelpBoard *bd = hp.board;
+    const int lane = threadIdx.x & 63;
+    const int turn = (int)(blockIdx.x & 63);
+    int64_t t0 = wall_clock64();
+    int seen = -1;
+    for (;;) {
+        const int done = uniform(agent_load(&bd->done));
+        if (done >= n_entries) return false;
+        const int64_t now = wall_clock64();
+        if (done != seen) {
+            seen = done;
+            t0 = now;
+        } else if (now - t0 > hp.limit) {
+            return false;
+        }
+        // lane l looks at slot (l + turn) mod 64, so that helpers spread
+        const int k = (lane + turn) & 63;
+        const unsigned long long tk = agent_load(bd->ticket + k);
+        const unsigned long long open = __ballot((int)(tk & 0xffff) < (int)((tk >> 16) & 0xffff));
+        if (open) {
+            const int at = (__ffsll(open) - 1 + turn) & 63;
+            unsigned long long got = 0;
+            if (lane == 0) got = help_take(bd->ticket + at);
+            const int lo = uniform((int)(unsigned)got), hi = uniform((int)(unsigned)(got >> 32));
+            if ((lo & 0xffff) < ((lo >> 16) & 0xffff)) {
+                hp.slot = at;
+                hp.epoch = hi;
+                hp.tile = lo & 0xffff;
+                return true;
+            }
+        } else {
+            // 14 us: hundreds of idle workgroups looking more often slow the others' accesses
+            for (int z = 0; z < 4; ++z) __builtin_amdgcn_s_sleep(127);
+        }
+    }
+}
+
 // One model evaluation at u (LDS): chi^2, g = J^T W r and A = J^T W J
 // (internal LM variables), written to out_chi2/out_g/out_A (LDS, A full
 // P x P).  All threads of the workgroup call it.
@@ -947,17 +1203,41 @@ __device__ inline void boot_weights(const BootArgs &bt, int64_t pix0, float (&m)
 // A team of tsize workgroups shares one evaluation: the workgroup of rank
 // trank takes the tiles whose row-major index is trank modulo tsize, and its
 // outputs are the partial sums over those tiles (tsize = 1: the whole image).
+//
+// With helpers (hp.role) the tiles of the image are shared as described above;
+// a helper makes one tile's planes and returns.
 template <class F, int KT, int NG>
 __device__ void evaluate(const double *u, const ModelArgs &ma, const BatchArgs &ba, const Meta &me, EvalShared<F> &sh,
                          float *planes, double *out_chi2, double *out_g, double *out_A,
-                         const BootArgs &bt = BootArgs{0u, 0u, 0, -1}, int trank = 0, int tsize = 1)
+                         const BootArgs &bt = BootArgs{0u, 0u, 0, -1}, int trank = 0, int tsize = 1,
+                         HelpState *hp = nullptr, int *sh_help = nullptr, int src = 0)
 {
     constexpr int P = F::P;
     constexpr int NR = 1 + P + P * (P + 1) / 2;
     const int H = me.h, W = me.w, K = me.k;
     const int tid = threadIdx.x;
+    const int nty = (H + TILE - 1) / TILE, ntx = (W + TILE - 1) / TILE;
+    const int ntiles = nty * ntx;
     const float *psl = stage_psf<F, NG>(planes, ba.psf + uniform64(me.psf_off), K);
-    eval_prologue<F>(u, ma, H, W, sh, planes);
+    int role = hp ? hp->role : HELP_NONE;
+    if (role == HELP_HELPER) {
+        const unsigned long long *d = reinterpret_cast<const unsigned long long *>(hp->buf());
+        unsigned long long *e = reinterpret_cast<unsigned long long *>(&sh);
+        for (int i = tid; i < (int)(help_head_bytes<F>() / 8); i += NT) e[i] = agent_load(d + i);
+        __syncthreads();
+    } else {
+        // a fit of several tiles asks for helpers when there is one for every
+        // four running fits (fewer give back less than sharing costs)
+        if (hp && hp->board && tid == NT - 1) {
+            const int running = hp->n_entries - agent_load(&hp->board->done);
+            sh_help[0] = ntiles > 1 && 4 * agent_load(&hp->board->idle) >= running;
+        }
+        eval_prologue<F>(u, ma, H, W, sh, planes);
+        if (hp && hp->board && uniform(sh_help[0]) > 0) {
+            role = help_claim<F>(*hp, sh_help) ? HELP_OWNER : HELP_NONE;
+            if (role == HELP_OWNER) help_open<F>(sh, *hp, src, ntiles);
+        }
+    }
     const cfloat *psf = (const cfloat *)(ba.psf + uniform64(me.psf_off));
     // Per-thread partial sums: chi^2 in FP64 (it decides accept/reject), g and
     // A in FP32 over at most FLUSH_TILES tiles (64 pixels), then FP64.
@@ -967,64 +1247,101 @@ __device__ void evaluate(const double *u, const ModelArgs &ma, const BatchArgs &
     for (int q = 0; q < NR - 1; ++q) red[q] = 0.0f;
     int r, cg;
     strip_of(tid, K, r, cg);
-    const int nty = (H + TILE - 1) / TILE, ntx = (W + TILE - 1) / TILE;
     const int lane = tid & 63, wave = tid >> 6;
-    const int ntiles = nty * ntx;
     const int mine = (ntiles - trank + tsize - 1) / tsize;        // tiles of this workgroup
     const bool flushes = mine > FLUSH_TILES;                      // uniform over the workgroup
     if (flushes && lane == 0)
         for (int q = 0; q < NR - 1; ++q) sh.nacc[wave][q] = 0.0;
     int since_flush = 0;
-    for (int ti = trank; ti < ntiles; ti += tsize) {
-        {
-            const int ty = ti / ntx, tx = ti - ty * ntx;
-            if (since_flush == FLUSH_TILES) {
-                // the FP32 partials of the last FLUSH_TILES tiles into the wave's FP64 sums
-#pragma unroll
-                for (int q = 0; q < NR - 1; ++q) {
-                    const double v = strip_sum((double)red[q], K);
-                    if (lane == 0) sh.nacc[wave][q] += v;
-                    red[q] = 0.0f;
-                }
-                since_flush = 0;
+    int next = trank;                                             // the first tile not yet added
+    int held = -1, drained = 0, lost = 0;                         // thread 0: help_next
+    while (next < ntiles) {
+        int ti = next, mode = TILE_SUM;
+        if (role == HELP_OWNER) {
+            __syncthreads();
+            if (tid == 0) {
+                sh_help[1] = help_next(*hp, next, ntiles, held, drained, sh_help[0], lost);
+                sh_help[2] = lost;
             }
-            ++since_flush;
-            const int ti0 = ty * TILE, tj0 = tx * TILE;
-            double acc0[4];
-            float acc[F::NPL][4];
-            tile_planes<F, KT, NG>(sh, planes, H, W, K, ti0, tj0, psf, psl, r, cg, acc0, acc);
-            const int i = ti0 + r;
-            if (i < H) {
-                float bw[4] = {1.0f, 1.0f, 1.0f, 1.0f};
-                if (bt.r >= 0) boot_weights(bt, (int64_t)i * W + tj0 + 4 * cg, bw);
-                float dv[4], wv[4];
-                strip_weights(ba, me.img_off + (int64_t)i * W, tj0 + 4 * cg, W, dv, wv);
+            __syncthreads();
+            ti = uniform(sh_help[0]);
+            mode = uniform(sh_help[1]);
+        } else if (role == HELP_HELPER) {
+            ti = hp->tile;
+            mode = TILE_STORE;
+        }
+        const int ty = ti / ntx, tx = ti - ty * ntx;
+        const int ti0 = ty * TILE, tj0 = tx * TILE;
+        double acc0[4];
+        float acc[F::NPL][4];
+        if (mode != TILE_LOAD) tile_planes<F, KT, NG>(sh, planes, H, W, K, ti0, tj0, psf, psl, r, cg, acc0, acc);
+        if (mode == TILE_STORE) {
+            HelpSlot *hs = hp->board->slot + hp->slot;
+            if (role == HELP_HELPER) {
+                // room in the ring: tile - kHelpRing has been added
+                if (tid == 0) {
+                    const int64_t t0 = wall_clock64();
+                    int ok = 1;
+                    while (agent_load(&hs->added) <= ti - kHelpRing && ok)
+                        if (wall_clock64() - t0 > hp->limit) ok = 0;
+                    sh_help[1] = ok;
+                }
+                __syncthreads();
+                if (uniform(sh_help[1]) == 0) return;
+            }
+            help_strip<F, true>(hp->buf(), ti, acc0, acc);
+            help_publish(hs->seq + ti % kHelpRing, help_seq(hp->epoch, ti));
+            if (role == HELP_HELPER) return;
+            continue;
+        }
+        if (mode == TILE_LOAD) help_strip<F, false>(hp->buf(), ti, acc0, acc);
+        next += tsize;
+        if (since_flush == FLUSH_TILES) {
+            // the FP32 partials of the last FLUSH_TILES tiles into the wave's FP64 sums
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int j = tj0 + 4 * cg + t;
-                    if (j >= W) continue;
-                    const float d = dv[t];
-                    const float wgt = wv[t] * bw[t];
-                    if (wgt == 0.0f) continue;
-                    const double pdx = ((double)j + 0.5) - 0.5 * W, pdy = 0.5 * H - ((double)i + 0.5);
-                    const double res = (double)d - (acc0[t] + F::sky_at(sh.prep, pdx, pdy));
-                    c2 = fma((double)wgt * res, res, c2);
-                    const float wr = wgt * (float)res;
-                    const float fdx = (float)pdx, fdy = (float)pdy;
+            for (int q = 0; q < NR - 1; ++q) {
+                const double v = strip_sum((double)red[q], K);
+                if (lane == 0) sh.nacc[wave][q] += v;
+                red[q] = 0.0f;
+            }
+            since_flush = 0;
+        }
+        ++since_flush;
+        const int i = ti0 + r;
+        if (i < H) {
+            float bw[4] = {1.0f, 1.0f, 1.0f, 1.0f};
+            if (bt.r >= 0) boot_weights(bt, (int64_t)i * W + tj0 + 4 * cg, bw);
+            float dv[4], wv[4];
+            strip_weights(ba, me.img_off + (int64_t)i * W, tj0 + 4 * cg, W, dv, wv);
 #pragma unroll
-                    for (int k = 0; k < P; ++k) {
-                        const float Jk = jac_at<F>(k, t, acc0, acc, fdx, fdy);
-                        red[k] = fmaf(wr, Jk, red[k]);
-                        const float wj = wgt * Jk;
+            for (int t = 0; t < 4; ++t) {
+                const int j = tj0 + 4 * cg + t;
+                if (j >= W) continue;
+                const float d = dv[t];
+                const float wgt = wv[t] * bw[t];
+                if (wgt == 0.0f) continue;
+                const double pdx = ((double)j + 0.5) - 0.5 * W, pdy = 0.5 * H - ((double)i + 0.5);
+                const double res = (double)d - (acc0[t] + F::sky_at(sh.prep, pdx, pdy));
+                c2 = fma((double)wgt * res, res, c2);
+                const float wr = wgt * (float)res;
+                const float fdx = (float)pdx, fdy = (float)pdy;
 #pragma unroll
-                        for (int l = 0; l <= k; ++l) {
-                            const float Jl = jac_at<F>(l, t, acc0, acc, fdx, fdy);
-                            red[P + k * (k + 1) / 2 + l] = fmaf(wj, Jl, red[P + k * (k + 1) / 2 + l]);
-                        }
+                for (int k = 0; k < P; ++k) {
+                    const float Jk = jac_at<F>(k, t, acc0, acc, fdx, fdy);
+                    red[k] = fmaf(wr, Jk, red[k]);
+                    const float wj = wgt * Jk;
+#pragma unroll
+                    for (int l = 0; l <= k; ++l) {
+                        const float Jl = jac_at<F>(l, t, acc0, acc, fdx, fdy);
+                        red[P + k * (k + 1) / 2 + l] = fmaf(wj, Jl, red[P + k * (k + 1) / 2 + l]);
                     }
                 }
             }
         }
+    }
+    if (role == HELP_OWNER && uniform(sh_help[2]) != 0) {
+        hp->board = nullptr;          // a tile never came: no more helpers for this fit, the slot stays claimed
+        hp->slot = -1;
     }
     // fixed-order reduction in FP64: within each wave, then the waves in order
     // (the plane buffer is idle after the last tile's barrier: reuse it)
@@ -1255,6 +1572,7 @@ struct LMShared {
     int t, status, fresh, apd, action, max_iter;
     int gal;
     int tok;                  // team: the last wait ended in time
+    int help[3];              // helpers: idle count, then tile / mode / lost of the next step
 };
 
 struct FitArgs {
@@ -1291,6 +1609,12 @@ struct FitArgs {
     double *part;
     int64_t part_stride;
     int64_t spin_limit;
+    // Helpers (nullable; one workgroup per fit only): HelpBoard.
+    struct HelpBoard *help;
+    char *help_buf;
+    int64_t help_stride;      // bytes of help_buf per slot
+    int help_slots;
+    int grid_items;           // workgroups worth launching (at least the queue entries)
 };
 
 enum { ACT_EVAL = 0, ACT_RETRY = 1, ACT_DONE = 2 };
@@ -1759,9 +2083,20 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
         if (tid == 0) s.gal = atomicAdd(fa.queue, 1);
         __syncthreads();
         const int qi = uniform(s.gal);
-        if (qi >= fa.n_gal) break;
-        int g, trank = 0, tsize = 1, team = 0;
-        if (fa.items) {
+        HelpState hp;
+        hp.board = fa.help;
+        hp.base = fa.help_buf;
+        hp.stride = fa.help_stride;
+        hp.n_slots = fa.help_slots;
+        hp.n_entries = fa.n_gal;
+        hp.limit = fa.spin_limit;
+        const bool helper = qi >= fa.n_gal;
+        if (helper && !fa.help) break;
+        int g = 0, trank = 0, tsize = 1, team = 0;
+        if (helper) {
+            hp.role = HELP_HELPER;
+            if (tid == 0) __hip_atomic_fetch_add(&fa.help->idle, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else if (fa.items) {
             const TeamItem it = fa.items[qi];
             g = uniform(it.fit);
             trank = uniform(it.rank);
@@ -1770,22 +2105,42 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
         } else {
             g = uniform(fa.order[qi]);
         }
-        if (fa.active && uniform(fa.active[g]) == 0) {
+        if (!helper && fa.active && uniform(fa.active[g]) == 0) {
+            if (fa.help && tid == 0)
+                __hip_atomic_fetch_add(&fa.help->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();      // s.gal is rewritten by thread 0 next
             continue;
         }
-        const int src = fa.n_boot > 0 ? g / fa.n_boot : g;
+        int src = fa.n_boot > 0 ? g / fa.n_boot : g;
         const BootArgs bt{fa.boot_k0, fa.boot_k1, src, fa.n_boot > 0 ? g - src * fa.n_boot : -1};
-        const Meta me = ba.meta[src];
+        Meta me = ba.meta[src];
         const bool member = trank > 0;
         TeamCtl *ctl = tsize > 1 ? fa.ctl + team : nullptr;
         double *slots = tsize > 1 ? fa.part + (int64_t)team * fa.part_stride : nullptr;
         // phase 0: the fit from params; phase 1: the refit from refit_start
         const bool refit = fa.refit_start != nullptr;
-        const int first = (!member && refit && fa.valid && uniform(fa.valid[g]) == 0) ? 1 : 0;
+        const int first = (!member && !helper && refit && fa.valid && uniform(fa.valid[g]) == 0) ? 1 : 0;
         int t0 = 0, phase = first, epoch = 0;
-        bool phase_start = !member;
+        bool phase_start = !member && !helper;
         for (;;) {
+            if (helper) {
+                if (tid < 64) {
+                    const bool any = help_find(hp, fa.n_gal);
+                    if (tid == 0) {
+                        s.action = any ? ACT_EVAL : ACT_DONE;
+                        s.help[0] = hp.slot;
+                        s.help[1] = hp.epoch;
+                        s.help[2] = hp.tile;
+                    }
+                }
+                __syncthreads();
+                if (uniform(s.action) == ACT_DONE) break;
+                hp.slot = uniform(s.help[0]);
+                hp.epoch = uniform(s.help[1]);
+                hp.tile = uniform(s.help[2]);
+                src = uniform(agent_load(&fa.help->slot[hp.slot].src));
+                me = ba.meta[src];
+            }
             if (phase_start) {
                 if (tid == 0) {
                     load_u<F>(s, ma, (phase ? fa.refit_start : fa.params) + (int64_t)g * ma.p);
@@ -1824,8 +2179,13 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
             }
             if (act == ACT_EVAL) {
                 if (tsize > 1 && !member) team_publish<F>(s, ctl, epoch);
-                // the evaluation site: the whole image, or this rank's tiles of it
-                evaluate<F, KT, NG>(s.ut, ma, ba, me, esh, planes, &s.chi2t, s.gt, s.At, bt, trank, tsize);
+                // the evaluation site: the whole image, this rank's tiles of it, or one tile for its owner
+                evaluate<F, KT, NG>(s.ut, ma, ba, me, esh, planes, &s.chi2t, s.gt, s.At, bt, trank, tsize,
+                                    &hp, s.help, src);
+                if (helper) {
+                    __syncthreads();
+                    continue;
+                }
                 if (tsize > 1) {
                     team_deliver<F::P>(ctl, slots + (int64_t)trank * NR, s.chi2t, s.gt, s.At);
                     if (!member && !team_collect<F>(s, ctl, slots, tsize, epoch, fa.spin_limit)) {
@@ -1842,9 +2202,15 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
             if (!member && tid < 64) lm_step_wave<F>(s, fa, me.h, me.w);
             __syncthreads();
         }
+        if (helper) break;
         if (member) {
             __syncthreads();          // s.gal is rewritten by thread 0 next
             continue;
+        }
+        if (tid == 0 && fa.help) {
+            if (hp.slot >= 0)
+                agent_store(&fa.help->slot[hp.slot].owner, 0);
+            __hip_atomic_fetch_add(&fa.help->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if (tsize > 1 && tid == 0) {
             // end the team (epoch + 2 exceeds every epoch a member can be waiting for)
@@ -2246,6 +2612,13 @@ __global__ void guess_stored_kernel(ModelArgs ma, int n_gal, const double *mom8,
 }
 
 static __global__ void fill_int_kernel(int *p, int v) { *p = v; }
+
+// The work queue's counter and, if given, the helpers' board, zeroed before a launch.
+static __global__ void fit_reset_kernel(int *queue, int *board, int n)
+{
+    if (threadIdx.x == 0) *queue = 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) board[i] = 0;
+}
 
 static __global__ void fill_ints_kernel(int *p, int n, int v)
 {
