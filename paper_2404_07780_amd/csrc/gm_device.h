@@ -178,36 +178,57 @@ __device__ inline double wave_scan(double v, int lane)
     return v + off;
 }
 
+// What the Sersic prologue needs besides the b_n iteration itself, made by the
+// other waves while wave 0 starts it (prologue_parts) and left in LDS.
+struct SersicParts {
+    double lga, lga1;         // ln Gamma(a), ln Gamma(a + 1), a = 2n (wave 1)
+    double psi1;              // psi(a + 1) (wave 2)
+    double ps[64];            // sum_{j=1..l} 1 / (a + j) at lane l (wave 2)
+    double l2pqn;             // ln(2 pi q n) (wave 3)
+};
+
 // P(a, x) (regularised lower incomplete gamma) and dP/da, one wave: lane l
 // sums the terms k = l, l + 64, l + 128 of the series P = sum_k T_k,
 // T_k = e^-x x^(a+k) / Gamma(a+k+1), dT_k/da = T_k (ln x - psi(a+k+1)).
 // ln Gamma(a+k+1) = ln Gamma(a+1) + sum_{j=1..k} ln(a+j) and
 // psi(a+k+1) = psi(a+1) + sum_{j=1..k} 1/(a+j) are prefix sums over the
-// lanes (lga1 = ln Gamma(a+1), psi1 = psi(a+1)).  192 terms cover
+// lanes (lga1 = ln Gamma(a+1), psi1 = psi(a+1)); those of the first 64 terms,
+// which do not depend on x, are given (lg0, ps0).  192 terms cover
 // x <= a + 20 for a <= 20 to double precision; a block of 64 terms is
 // skipped once the last term of the previous block is below 1e-17 of the
 // sum and the ratio of successive terms, x / (a + k), is below 1/2 (the rest
-// of the series is then below twice that last term).
-__device__ inline void gammainc_wave(double a, double x, double lga1, double psi1, int lane, bool want_da, double *P,
-                                     double *dPda)
+// of the series is then below twice that last term).  lx = ln x.
+__device__ inline void gammainc_wave(double a, double x, double lx, double lga1, double lg0, double psi1, double ps0,
+                                     int lane, bool want_da, double *P, double *dPda)
 {
-    double lx = log(x), sp = 0.0, sd = 0.0, clg = lga1, cps = psi1;
+    double sp = 0.0, sd = 0.0, clg = lga1, cps = psi1, sum = 0.0;
 #pragma unroll 1
     for (int m = 0; m < 3; ++m) {
         const double k = (double)(lane + 64 * m);
-        const double lg = wave_scan(k >= 1.0 ? log(a + k) : 0.0, lane);
+        const double lg = m == 0 ? lg0 : wave_scan(log(a + k), lane);
         const double T = exp((a + k) * lx - x - (clg + lg));
         sp += T;
         clg += lane_value(lg, 63);
         if (want_da) {
-            const double ps = wave_scan(k >= 1.0 ? 1.0 / (a + k) : 0.0, lane);
+            const double ps = m == 0 ? ps0 : wave_scan(1.0 / (a + k), lane);
             sd += T * (lx - (cps + ps));
             cps += lane_value(ps, 63);
         }
-        if (m < 2 && x < 0.5 * (a + 64.0 * (m + 1)) && lane_value(T, 63) < 1e-17 * wave_sum(sp)) break;
+        sum = wave_sum(sp);
+        if (m < 2 && x < 0.5 * (a + 64.0 * (m + 1)) && lane_value(T, 63) < 1e-17 * sum) break;
     }
-    *P = wave_sum(sp);
+    *P = sum;
     if (want_da) *dPda = wave_sum(sd);
+}
+
+// The prefix sums of gammainc_wave's first block.
+__device__ inline double gamma_lg0(double a, int lane)
+{
+    return wave_scan(lane >= 1 ? log(a + (double)lane) : 0.0, lane);
+}
+__device__ inline double gamma_ps0(double a, int lane)
+{
+    return wave_scan(lane >= 1 ? 1.0 / (a + (double)lane) : 0.0, lane);
 }
 
 // nu_n of the Sersic law (the b_n of Sec. 4.1): the root of P(2n, b) = 1/2,
@@ -216,36 +237,39 @@ __device__ inline void gammainc_wave(double a, double x, double lga1, double psi
 // the error after a Newton step, about |f''/(2 f')| step^2 with
 // f''/f' = (a - 1)/b - 1, is below 1e-16 b (or a step is below 1e-14 b);
 // db/dn by implicit differentiation, -2 (dP/da) / (dP/dx).  All lanes of
-// one wave.  Also returns ln Gamma(2n) and psi(2n) (= psi(2n + 1) - 1/(2n)),
-// which the solve computes on the way.
-__device__ inline double sersic_b_wave(double n, int lane, double *dbdn, double *lg2n, double *psi2n)
+// one wave; b0: sersic_b0, lg0: gamma_lg0.  Also returns ln b.
+__device__ inline double sersic_b0(double n)
 {
-    double a = 2.0 * n, lo = 0.0, hi = a + 20.0;
-    double in = 1.0 / n;
-    double b = a - 1.0 / 3.0 + in * (4.0 / 405.0 + in * (46.0 / 25515.0 + in * (131.0 / 1148175.0)));
-    if (!(b > lo && b < hi)) b = 0.5 * a;
-    const double lga = lgamma(a), lga1 = lga + log(a);
+    const double a = 2.0 * n, in = 1.0 / n;
+    const double b = a - 1.0 / 3.0 + in * (4.0 / 405.0 + in * (46.0 / 25515.0 + in * (131.0 / 1148175.0)));
+    return b > 0.0 && b < a + 20.0 ? b : 0.5 * a;
+}
+__device__ inline double sersic_b_wave(double n, double b0, double lb0, double lg0, const SersicParts &pt, int lane,
+                                       double *dbdn, double *lnb)
+{
+    double a = 2.0 * n, lo = 0.0, hi = a + 20.0, b = b0, lb = lb0;
+    const double lga = pt.lga, lga1 = pt.lga1;
 #pragma unroll 1
     for (int it = 0; it < 60; ++it) {
         double P;
-        gammainc_wave(a, b, lga1, 0.0, lane, false, &P, nullptr);
+        const double fp = exp((a - 1.0) * lb - b - lga);
+        gammainc_wave(a, b, lb, lga1, lg0, 0.0, 0.0, lane, false, &P, nullptr);
         double f = P - 0.5;
         if (f > 0.0) hi = b; else lo = b;
-        double fp = exp((a - 1.0) * log(b) - b - lga);
         double nb = b - f / fp;
         const bool newton = nb > lo && nb < hi;
         if (!newton) nb = 0.5 * (lo + hi);
         double st = fabs(nb - b);
         const double pred = 0.5 * fabs((a - 1.0) / b - 1.0) * st * st;
         b = nb;
+        lb = log(b);
         if (st < 1e-14 * b || (newton && pred < 1e-16 * b)) break;
     }
     double P, dPa;
-    const double psi1 = digamma(a + 1.0);
-    gammainc_wave(a, b, lga1, psi1, lane, true, &P, &dPa);
-    *dbdn = -2.0 * dPa / exp((a - 1.0) * log(b) - b - lga);
-    *lg2n = lga;
-    *psi2n = psi1 - 1.0 / a;
+    const double fp = exp((a - 1.0) * lb - b - lga);
+    gammainc_wave(a, b, lb, lga1, lg0, pt.psi1, pt.ps[lane], lane, true, &P, &dPa);
+    *dbdn = -2.0 * dPa / fp;
+    *lnb = lb;
     return b;
 }
 
@@ -386,7 +410,9 @@ __device__ inline float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 // ---------------------------------------------------------------- components
 // Every component type provides: its LM slots (NS, kind(s)), the slots of
 // its axis ratio, angle and scales (canonical form), an FP64 prologue
-// prep(us, cst, ...) from its slot values us (u-space) and shape constants cst,
+// prep(us, cst, ..., pre) of one wave from its slot values us (u-space) and
+// shape constants cst -- preceded, where PARTS, by a step in which every wave
+// w makes its share parts(us, ..., w, lane, pre) of Pre (LDS) --
 // a point evaluation pt<F64>(k, dx, dy, I, d) of the light I (FP64 if F64)
 // and its FP32 derivatives d[s] = dI/du_s, and the moment-based start values.
 
@@ -403,16 +429,57 @@ struct Sersic {
     {
         return s == 0 ? KX0 : s == 1 ? KY0 : s == 2 ? KMAG : s == 3 ? KSCALE : s == 4 ? KN : s == 5 ? KQ : KPA;
     }
-    // all lanes of wave 0 call this (the b_n series is spread over the lanes)
-    __device__ static void prep(const double *u, const double *, double m0, int H, int W, int osf, int osw, int lane,
-                                K &k)
+    // The waves' shares: wave 0 the start of the b_n iteration (kept in its
+    // registers: Start), the others what Pre holds.  One wave doing all of it
+    // in turn took 15.5k cycles per evaluation, two thirds of the prologue.
+    static constexpr bool PARTS = true;
+    struct Pre {
+        SersicParts s;
+        Geo g;
+    };
+    struct Start {
+        double n, b0, lb0, lg0;
+    };
+    __device__ static Start parts(const double *u, int H, int W, int osf, int osw, int w, int lane, Pre &pre)
     {
-        double x0 = u[0], y0 = u[1], m = u[2], lnre = u[3], lnn = u[4], q = u[5], th = u[6];
-        double n = exp(lnn);
-        double bp, lg2n, psi;
-        double b = sersic_b_wave(n, lane, &bp, &lg2n, &psi);
-        double lnIe = -0.4 * kLn10 * (m - m0) + 2.0 * n * log(b) - log(2.0 * kPi * q * n) - 2.0 * lnre - lg2n - b;
-        geo_prep(x0, y0, q, th, H, W, osf, osw, k.g);
+        const double n = exp(u[4]), a = 2.0 * n;
+        Start st{n, 0.0, 0.0, 0.0};
+        if (w == 0) {
+            st.b0 = sersic_b0(n);
+            st.lb0 = log(st.b0);
+            st.lg0 = gamma_lg0(a, lane);
+        } else if (w == 1) {
+            const double lga = lgamma(a), lga1 = lga + log(a);
+            if (lane == 0) {
+                pre.s.lga = lga;
+                pre.s.lga1 = lga1;
+            }
+        } else if (w == 2) {
+            const double ps = gamma_ps0(a, lane), psi1 = digamma(a + 1.0);
+            pre.s.ps[lane] = ps;
+            if (lane == 0) pre.s.psi1 = psi1;
+        } else {
+            Geo g;
+            geo_prep(u[0], u[1], u[5], u[6], H, W, osf, osw, g);
+            const double l = log(2.0 * kPi * u[5] * n);
+            if (lane == 0) {
+                pre.g = g;
+                pre.s.l2pqn = l;
+            }
+        }
+        return st;
+    }
+    // all lanes of wave 0 call this (the b_n series is spread over the lanes)
+    __device__ static void prep(const double *u, const double *, double m0, int, int, int, int, int lane,
+                                const Start &st, const Pre &pre, K &k)
+    {
+        double m = u[2], lnre = u[3];
+        const double n = st.n;
+        double bp, lb;
+        double b = sersic_b_wave(n, st.b0, st.lb0, st.lg0, pre.s, lane, &bp, &lb);
+        const double lg2n = pre.s.lga, psi = pre.s.psi1 - 1.0 / (2.0 * n);
+        double lnIe = -0.4 * kLn10 * (m - m0) + 2.0 * n * lb - pre.s.l2pqn - 2.0 * lnre - lg2n - b;
+        k.g = pre.g;
         k.lnIe = lnIe;
         k.b = b;
         k.inv2n = 0.5 / n;
@@ -427,7 +494,7 @@ struct Sersic {
         k.l2re2f = (float)(2.0 * lnre * kLog2e);
         k.bnf = (float)(b / n);
         // d ln I / d ln n = cn - n b' z + b z ln(r^2/re^2) / (2n)
-        k.cnf = (float)(n * (2.0 * log(b) + 2.0 * n * bp / b - 2.0 * psi) - 1.0);
+        k.cnf = (float)(n * (2.0 * lb + 2.0 * n * bp / b - 2.0 * psi) - 1.0);
         k.nbpf = (float)(n * bp);
         k.bl2nf = (float)(b * kLn2 / (2.0 * n));
     }
@@ -486,10 +553,17 @@ struct SersicBox {
     };
     static constexpr int NS = 8, IQ = 5, ITH = 6, IS0 = 3, IS1 = -1;
     __host__ __device__ static constexpr int kind(int s) { return s == 7 ? KBOX : Sersic::kind(s); }
-    __device__ static void prep(const double *u, const double *cst, double m0, int H, int W, int osf, int osw,
-                                int lane, K &k)
+    static constexpr bool PARTS = true;
+    typedef Sersic::Pre Pre;
+    typedef Sersic::Start Start;
+    __device__ static Start parts(const double *u, int H, int W, int osf, int osw, int w, int lane, Pre &pre)
     {
-        Sersic::prep(u, cst, m0, H, W, osf, osw, lane, k);
+        return Sersic::parts(u, H, W, osf, osw, w, lane, pre);
+    }
+    __device__ static void prep(const double *u, const double *cst, double m0, int H, int W, int osf, int osw,
+                                int lane, const Start &st, const Pre &pre, K &k)
+    {
+        Sersic::prep(u, cst, m0, H, W, osf, osw, lane, st, pre, k);
         const double c = u[7] + 2.0, ic = 1.0 / c;
         const double lnrbox = log(0.5 * kPi * c) - (2.0 * lgamma(ic) - lgamma(2.0 * ic));
         k.lnIe += lnrbox;
@@ -582,6 +656,7 @@ struct ExpDisk {
     {
         return s == 0 ? KX0 : s == 1 ? KY0 : s == 2 ? KMAG : s == 3 ? KSCALE : s == 4 ? KQ : KPA;
     }
+    static constexpr bool PARTS = false;
     __device__ static void prep(const double *u, const double *, double m0, int H, int W, int osf, int osw, int,
                                 K &k)
     {
@@ -637,6 +712,7 @@ struct Ferrer {
     };
     static constexpr int NS = 6, IQ = 4, ITH = 5, IS0 = 3, IS1 = -1;
     __host__ __device__ static constexpr int kind(int s) { return ExpDisk::kind(s); }
+    static constexpr bool PARTS = false;
     __device__ static void prep(const double *u, const double *cst, double m0, int H, int W, int osf, int osw, int,
                                 K &k)
     {
@@ -714,6 +790,7 @@ struct King {
     {
         return s == 0 ? KX0 : s == 1 ? KY0 : s == 2 ? KAMP : s == 3 ? KSCALE : s == 4 ? KSCALE : s == 5 ? KQ : KPA;
     }
+    static constexpr bool PARTS = false;
     __device__ static void prep(const double *u, const double *cst, double, int H, int W, int osf, int osw, int,
                                 K &k)
     {
@@ -800,6 +877,7 @@ struct FerrerFree {
     };
     static constexpr int NS = 8, IQ = 4, ITH = 5, IS0 = 3, IS1 = -1;
     __host__ __device__ static constexpr int kind(int s) { return s == 6 ? KFA : s == 7 ? KFB : Ferrer::kind(s); }
+    static constexpr bool PARTS = false;
     __device__ static void prep(const double *u, const double *, double m0, int H, int W, int osf, int osw, int lane,
                                 K &k)
     {
@@ -873,6 +951,7 @@ struct KingFree {
     };
     static constexpr int NS = 8, IQ = 5, ITH = 6, IS0 = 3, IS1 = 4;
     __host__ __device__ static constexpr int kind(int s) { return s == 7 ? KKAL : King::kind(s); }
+    static constexpr bool PARTS = false;
     __device__ static void prep(const double *u, const double *, double m0, int H, int W, int osf, int osw, int lane,
                                 K &k)
     {
@@ -953,6 +1032,7 @@ struct Gaussian {
     {
         return s == 0 ? KX0 : s == 1 ? KY0 : s == 2 ? KAMP : s == 3 ? KSCALE : s == 4 ? KQ : KPA;
     }
+    static constexpr bool PARTS = false;
     __device__ static void prep(const double *u, const double *, double, int H, int W, int osf, int osw, int, K &k)
     {
         double sg = exp(u[3]) / (2.0 * sqrt(2.0 * kLn2));
@@ -1003,6 +1083,7 @@ struct Moffat {
     };
     static constexpr int NS = 6, IQ = 4, ITH = 5, IS0 = 3, IS1 = -1;
     __host__ __device__ static constexpr int kind(int s) { return ExpDisk::kind(s); }
+    static constexpr bool PARTS = false;
     __device__ static void prep(const double *u, const double *cst, double m0, int H, int W, int osf, int osw, int,
                                 K &k)
     {
@@ -1087,13 +1168,34 @@ struct FamSingle {
         typename C::K k0;
         double sky, gx, gy;
     };
-    __device__ static void prep(const double *u, const double *cst, double m0, int H, int W, int osf, int osw,
-                                int lane, Prep &p)
+    // The scalar prologue, all threads; scratch: LDS.  The result is in p after
+    // the caller's next barrier.
+    __device__ static void prep_all(const double *u, const double *cst, double m0, int H, int W, int osf, int osw,
+                                    int tid, void *scratch, Prep &p)
     {
-        C::prep(u, cst, m0, H, W, osf, osw, lane, p.k0);
-        p.sky = u[SKY];
-        p.gx = TILT ? u[SKY + 1] : 0.0;
-        p.gy = TILT ? u[SKY + 2] : 0.0;
+        const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+        auto put = [&](const typename C::K &k) {
+            if (lane == 0) {
+                p.k0 = k;
+                p.sky = u[SKY];
+                p.gx = TILT ? u[SKY + 1] : 0.0;
+                p.gy = TILT ? u[SKY + 2] : 0.0;
+            }
+        };
+        if constexpr (C::PARTS) {
+            auto &pre = *reinterpret_cast<typename C::Pre *>(scratch);
+            const auto st = C::parts(u, H, W, osf, osw, w, lane, pre);
+            __syncthreads();
+            if (w == 0) {
+                typename C::K k;
+                C::prep(u, cst, m0, H, W, osf, osw, lane, st, pre, k);
+                put(k);
+            }
+        } else if (w == 0) {
+            typename C::K k;
+            C::prep(u, cst, m0, H, W, osf, osw, lane, k);
+            put(k);
+        }
     }
     // the unconvolved sky at a pixel at (dx, dy) from the cutout's centre
     __device__ static double sky_at(const Prep &p, double dx, double dy)
@@ -1150,16 +1252,31 @@ struct FamPair {
         typename C2::K k1;
         double sky;
     };
-    __device__ static void prep(const double *u, const double *cst, double m0, int H, int W, int osf, int osw,
-                                int lane, Prep &p)
+    // The scalar prologue, all threads: C1 (a Sersic) as in FamSingle, C2 by
+    // wave 1 meanwhile.
+    __device__ static void prep_all(const double *u, const double *cst, double m0, int H, int W, int osf, int osw,
+                                    int tid, void *scratch, Prep &p)
     {
-        C1::prep(u, cst, m0, H, W, osf, osw, lane, p.k0);
-        double u2[C2::NS];
-        u2[0] = u[0];
-        u2[1] = u[1];
-        for (int s = 2; s < C2::NS; ++s) u2[s] = u[O2 + s];
-        C2::prep(u2, cst + 2, m0, H, W, osf, osw, lane, p.k1);
-        p.sky = u[SKY];
+        const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+        auto &pre = *reinterpret_cast<typename C1::Pre *>(scratch);
+        const auto st = C1::parts(u, H, W, osf, osw, w, lane, pre);
+        __syncthreads();
+        if (w == 0) {
+            typename C1::K k;
+            C1::prep(u, cst, m0, H, W, osf, osw, lane, st, pre, k);
+            if (lane == 0) {
+                p.k0 = k;
+                p.sky = u[SKY];
+            }
+        } else if (w == 1) {
+            double u2[C2::NS];
+            u2[0] = u[0];
+            u2[1] = u[1];
+            for (int s = 2; s < C2::NS; ++s) u2[s] = u[O2 + s];
+            typename C2::K k;
+            C2::prep(u2, cst + 2, m0, H, W, osf, osw, lane, k);
+            if (lane == 0) p.k1 = k;
+        }
     }
     __device__ static double sky_at(const Prep &p, double, double) { return p.sky; }
     __device__ static const Geo &geo(const Prep &p, int c) { return c == 0 ? p.k0.g : p.k1.g; }

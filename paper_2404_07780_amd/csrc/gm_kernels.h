@@ -114,6 +114,14 @@ __device__ inline double strip_sum(double v, int K)
     return ((lane_value(v, 7) + lane_value(v, 15)) + lane_value(v, 23)) + lane_value(v, 31);
 }
 
+// One row's eight strips (consecutive lanes' values in LDS), in the ladder's order.
+__device__ inline double strip_row(const float *p)
+{
+    const float4 a = *reinterpret_cast<const float4 *>(p), b = *reinterpret_cast<const float4 *>(p + 4);
+    return (((double)b.w + (double)b.z) + ((double)b.y + (double)b.x)) +
+           (((double)a.w + (double)a.z) + ((double)a.y + (double)a.x));
+}
+
 // Plane groups: plane 0 (FP64) counts two units, the others one; groups are
 // contiguous and balanced in units.
 __host__ __device__ constexpr int group_bound(int npl, int ng, int g)
@@ -157,6 +165,7 @@ struct EvalShared {
     typename F::Prep prep;
     double win0[F::NCOMP][MAXWIN];
     float win[F::NCOMP][MAXWIN][F::ND];
+    double c2[NWAVE];                                     // per-wave chi^2
     double nacc[NWAVE][F::P + F::P * (F::P + 1) / 2];     // per-wave FP64 sums of the flushed partials
 };
 
@@ -202,17 +211,13 @@ __device__ inline const float *stage_psf(float *planes, const float *psf, int K)
     return d;
 }
 
-// Scalar prologue (wave 0) + oversampled window tables (all threads).
+// Scalar prologue + oversampled window tables.
 // u: LDS (FP64, internal).  scratch: the idle plane buffer.
 template <class F>
 __device__ void eval_prologue(const double *u, const ModelArgs &ma, int H, int W, EvalShared<F> &sh, float *scratch)
 {
     const int tid = threadIdx.x;
-    if (tid < 64) {
-        typename F::Prep lp;
-        F::prep(u, ma.cst, ma.m0, H, W, ma.osf, ma.osw, tid, lp);
-        if (tid == 0) sh.prep = lp;
-    }
+    F::prep_all(u, ma.cst, ma.m0, H, W, ma.osf, ma.osw, tid, scratch, sh.prep);
     __syncthreads();
     const int f = ma.osf;
     const double invf = 1.0 / (double)f;
@@ -1343,34 +1348,55 @@ __device__ void evaluate(const double *u, const ModelArgs &ma, const BatchArgs &
         hp->board = nullptr;          // a tile never came: no more helpers for this fit, the slot stays claimed
         hp->slot = -1;
     }
-    // fixed-order reduction in FP64: within each wave, then the waves in order
-    // (the plane buffer is idle after the last tile's barrier: reuse it)
-    double *sred = reinterpret_cast<double *>(planes);
+    // Fixed-order reduction in FP64 through the idle plane buffer (after the last
+    // tile's barrier), in the order of strip_sum and then the waves: the FP32
+    // partials of as many sums as fit are written one row of NT floats per sum;
+    // a thread then adds the two strip rows of one of the four terms of a
+    // wave's sum, and another the four terms of each wave and the waves.
+    double *terms = reinterpret_cast<double *>(planes);           // [sum of the chunk][wave][4]
+    constexpr int QB = NWAVE * 4 * (int)sizeof(double) + NT * (int)sizeof(float);
+    const int chunk = min(NR - 1, (int)(lds_main_bytes<F, NG>(K) / QB));
+    const bool gap4 = strip_gap(region_wp(K)) == 4;
     {
-        double v = strip_sum(c2, K);
-        if (lane == 0) sred[wave * NR] = v;
+        const double v = strip_sum(c2, K);
+        if (lane == 0) sh.c2[wave] = v;
     }
+#pragma unroll 1
+    for (int q0 = 0; q0 < NR - 1; q0 += chunk) {
+        const int n = min(chunk, NR - 1 - q0);
+        float *rows = reinterpret_cast<float *>(terms + chunk * NWAVE * 4);
 #pragma unroll
-    for (int q = 1; q < NR; ++q) {
-        double v = strip_sum((double)red[q - 1], K);
-        if (lane == 0) sred[wave * NR + q] = flushes ? sh.nacc[wave][q - 1] + v : v;
-    }
-    __syncthreads();
-    for (int q = tid; q < NR; q += NT) {
-        double s = sred[q];
-        for (int wv = 1; wv < NWAVE; ++wv) s += sred[wv * NR + q];
-        if (q == 0) {
-            *out_chi2 = s;
-        } else if (q <= P) {
-            out_g[q - 1] = s;
-        } else {
-            int e = q - 1 - P, k = 0;
-            while ((k + 1) * (k + 2) / 2 <= e) ++k;
-            int l = e - k * (k + 1) / 2;
-            out_A[k * P + l] = s;
-            out_A[l * P + k] = s;
+        for (int q = 0; q < NR - 1; ++q)
+            if (q >= q0 && q < q0 + n) rows[(q - q0) * NT + tid] = red[q];
+        __syncthreads();
+        for (int t = tid; t < n * NWAVE * 4; t += NT) {
+            const int i = t & 3, w = (t >> 2) & (NWAVE - 1), q = t / (NWAVE * 4);
+            const float *p = rows + q * NT + 64 * w + (gap4 ? 16 * (i >> 1) + 32 * (i & 1) : 8 * i);
+            terms[t] = strip_row(p + (gap4 ? 8 : 32)) + strip_row(p);
         }
+        __syncthreads();
+        for (int q = tid; q < n; q += NT) {
+            double s = 0.0;
+            for (int w = 0; w < NWAVE; ++w) {
+                const double *t4 = terms + (q * NWAVE + w) * 4;
+                double v = ((t4[0] + t4[1]) + t4[2]) + t4[3];
+                if (flushes) v = sh.nacc[w][q0 + q] + v;
+                s = w == 0 ? v : s + v;
+            }
+            const int e = q0 + q;
+            if (e < P) {
+                out_g[e] = s;
+            } else {
+                int k = 0;
+                while ((k + 1) * (k + 2) / 2 <= e - P) ++k;
+                const int l = e - P - k * (k + 1) / 2;
+                out_A[k * P + l] = s;
+                out_A[l * P + k] = s;
+            }
+        }
+        __syncthreads();
     }
+    if (tid == 0) *out_chi2 = ((sh.c2[0] + sh.c2[1]) + sh.c2[2]) + sh.c2[3];
     __syncthreads();
 }
 
@@ -1566,10 +1592,11 @@ __device__ void fit_errors(double *A, double *g, const double *u, const int *fre
 template <class F>
 struct LMShared {
     double u[F::P], ut[F::P], g[F::P], gt[F::P], A[F::P * F::P], At[F::P * F::P];
-    double Dg[F::P], sig[F::P], delta[F::P];
+    double Dg[F::P], sig[F::P], un[F::P];        // un: the damped step's point
     double chi2, chi2t, lambda;
     int freev[F::P];
     int t, status, fresh, apd, action, max_iter;
+    int damped;               // the damped step: 1 factorised, 2 below the tolerance
     int gal;
     int tok;                  // team: the last wait ended in time
     int help[3];              // helpers: idle count, then tile / mode / lost of the next step
@@ -1699,33 +1726,27 @@ __device__ inline void team_deliver(TeamCtl *ctl, double *slot, double chi2, con
 }
 
 // ---------------------------------------------------------------- wave-parallel LM step
-// One wave runs the LM bookkeeping between evaluations.  Lane r < P holds row
+// Two waves run the LM bookkeeping between evaluations.  Lane r < P holds row
 // r of the P x P normal matrix; the Cholesky factorisation is row-parallel
-// (the pivot row is broadcast with readlane at every step), and the
-// triangular solves and the diagonal of the inverse are computed by every
-// lane from broadcast values.  Sums run in the same order as the textbook
+// (the pivot column is broadcast with readlane at every step), the triangular
+// solves are computed by every lane from broadcast values, the columns of the
+// inverse factor by a lane each.  Sums run in the same order as the textbook
 // one-thread algorithm.
 
-// L (lane r: row r) of M (lane r: row r); false if M is not positive definite.
+// L (lane r: row r) of M (lane r: row r, overwritten); false if M is not
+// positive definite.  Column by column, each column's products taken from the
+// rest of M at once: an element still sees them in increasing column order.
 template <int P>
-__device__ inline bool chol_rows(const double (&m)[P], double (&l)[P], int lane)
+__device__ inline bool chol_rows(double (&m)[P], double (&l)[P], int lane)
 {
 #pragma unroll
-    for (int k = 0; k < P; ++k) l[k] = 0.0;
-#pragma unroll
     for (int j = 0; j < P; ++j) {
-        double lj[P > 1 ? P - 1 : 1];
-#pragma unroll
-        for (int k = 0; k < j; ++k) lj[k] = lane_value(l[k], j);
-        double d = lane_value(m[j], j);
-#pragma unroll
-        for (int k = 0; k < j; ++k) d -= lj[k] * lj[k];
+        const double d = lane_value(m[j], j);
         if (!(d > 0.0) || !isfinite(d)) return false;
         const double ljj = sqrt(d);
-        double sr = m[j];
+        l[j] = lane > j ? m[j] / ljj : (lane == j ? ljj : 0.0);
 #pragma unroll
-        for (int k = 0; k < j; ++k) sr -= l[k] * lj[k];
-        l[j] = lane > j ? sr / ljj : (lane == j ? ljj : 0.0);
+        for (int c = j + 1; c < P; ++c) m[c] -= l[j] * lane_value(l[j], c);
     }
     return true;
 }
@@ -1751,24 +1772,20 @@ __device__ inline void chol_solve_rows(const double (&l)[P], const double (&b)[P
     }
 }
 
-// diag((L L^T)^-1)_c = sum_i (L^-1)_ic^2, as a wave-uniform array.
+// diag((L L^T)^-1)_c = sum_i (L^-1)_ic^2 at lane c (column c of L^-1 by lane c).
 template <int P>
-__device__ inline void chol_inv_diag_rows(const double (&l)[P], double (&dg)[P])
+__device__ inline double chol_inv_diag_lane(const double (&l)[P], int lane)
 {
+    double z[P], acc = 0.0;
 #pragma unroll
-    for (int c = 0; c < P; ++c) {
-        double z[P];
-        double acc = 0.0;
+    for (int i = 0; i < P; ++i) {
+        double t = (i == lane) ? 1.0 : 0.0;
 #pragma unroll
-        for (int i = c; i < P; ++i) {
-            double t = (i == c) ? 1.0 : 0.0;
-#pragma unroll
-            for (int k = c; k < i; ++k) t -= lane_value(l[k], i) * z[k];
-            z[i] = t / lane_value(l[i], i);
-            acc += z[i] * z[i];
-        }
-        dg[c] = acc;
+        for (int k = 0; k < i; ++k) t -= lane_value(l[k], i) * z[k];      // z[k] = 0 for k < c
+        z[i] = t / lane_value(l[i], i);
+        acc += z[i] * z[i];
     }
+    return acc;
 }
 
 // v limited to [lo, hi] by comparisons: a NaN stays NaN (fmin/fmax would
@@ -1804,7 +1821,7 @@ __device__ void clamp_u(double *u, int H, int W)
     for (int k = 0; k < F::P; ++k) u[k] = clamp_var<F>(k, u[k], H, W);
 }
 
-// Wave 0, all lanes: absorb the evaluation just made (the start point, or a
+// All threads: absorb the evaluation just made (the start point, or a
 // trial: accept if chi^2 decreased, else raise the damping), then choose the
 // next trial point or finish.
 //   Start: A, g from the evaluation, fixed rows/columns replaced by the
@@ -1817,10 +1834,18 @@ __device__ void clamp_u(double *u, int H, int W)
 //     of the current accepted A; a failed factorisation raises lambda by 10
 //     and counts the trial; lambda > 1e9 -> STALLED; max_iter trials ->
 //     MAXITER.
+// Waves 0 and 1 both absorb; wave 0 then factorises A (stop test) while wave 1
+// factorises A + lambda D (trial), and after a barrier wave 0 writes the
+// outcome.  (One wave doing both in turn: 10k cycles per step, now 6k.)
 template <class F>
-__device__ void lm_step_wave(LMShared<F> &s, const FitArgs &fa, int H, int W)
+__device__ void lm_step(LMShared<F> &s, const FitArgs &fa, int H, int W)
 {
     constexpr int P = F::P;
+    const int wave = uniform((int)(threadIdx.x >> 6));
+    if (wave > 1) {
+        __syncthreads();
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const bool row = lane < P;
     const int r = row ? lane : 0;
@@ -1870,95 +1895,112 @@ __device__ void lm_step_wave(LMShared<F> &s, const FitArgs &fa, int H, int W)
         for (int k = 0; k < P; ++k) a[k] = s.A[r * P + k];
         gr = s.g[r];
     }
-    double utr = ur;
-    bool proposed = false;
-    if (action != ACT_DONE) {
-        if (t >= s.max_iter) {
-            status = GM_ST_MAXITER;
-            action = ACT_DONE;
-        } else {
-            t += 1;
-            double gv[P];
+    if (action != ACT_DONE && t >= s.max_iter) {
+        status = GM_ST_MAXITER;
+        action = ACT_DONE;
+    }
+    const bool step = action != ACT_DONE;
+    double utr = ur, gv[P];
+    bool stop = false;
+    if (step) {
+        t += 1;
 #pragma unroll
-            for (int k = 0; k < P; ++k) gv[k] = lane_value(gr, k);
-            bool stop = false;
-            if (fresh) {
-                double drr = 0.0;
+        for (int k = 0; k < P; ++k) gv[k] = lane_value(gr, k);
+        if (fresh) {
+            double drr = 0.0;
 #pragma unroll
-                for (int k = 0; k < P; ++k)
-                    if (k == r) drr = a[k];
-                double amax = 0.0;
+            for (int k = 0; k < P; ++k)
+                if (k == r) drr = a[k];
+            double amax = 0.0;
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                const double dk = lane_value(drr, k);
+                if (fv[k] && dk > amax) amax = dk;
+            }
+            dgr = fr ? (drr > 1e-12 * amax ? drr : 1e-12 * amax) : 1.0;
+        }
+    }
+    if (wave == 1) {
+        // the damped step; conv: its test against 1/sqrt(D_kk), for an A that is not positive definite
+        if (step) {
+            double m[P], l[P];
+#pragma unroll
+            for (int k = 0; k < P; ++k) m[k] = a[k] + (k == r ? lambda * dgr : 0.0);
+            const bool ok = chol_rows<P>(m, l, lane);
+            bool conv = false;
+            if (ok) {
+                double dv[P];
+                chol_solve_rows<P>(l, gv, dv);
+                const double sg = fresh ? 1.0 / sqrt(dgr) : sgr;
+                double smax = 0.0;
 #pragma unroll
                 for (int k = 0; k < P; ++k) {
-                    const double dk = lane_value(drr, k);
-                    if (fv[k] && dk > amax) amax = dk;
+                    const double q = fabs(dv[k]) / lane_value(sg, k);
+                    if (!(q <= smax)) smax = q;
                 }
-                dgr = fr ? (drr > 1e-12 * amax ? drr : 1e-12 * amax) : 1.0;
-                double l[P];
-                apd = chol_rows<P>(a, l, lane) ? 1 : 0;
-                if (apd) {
-                    double idg[P], dv[P];
-                    chol_inv_diag_rows<P>(l, idg);
-                    chol_solve_rows<P>(l, gv, dv);
-                    double smax = 0.0;
+                conv = smax < fa.tol;
+                double dr = 0.0;
 #pragma unroll
-                    for (int k = 0; k < P; ++k) {
-                        const double sk = sqrt(idg[k]);
-                        if (k == r) sgr = sk;
-                        const double q = fabs(dv[k]) / sk;
-                        if (!(q <= smax)) smax = q;
-                    }
-                    if (smax < fa.tol) {
-                        t -= 1;
-                        status = GM_ST_CONVERGED;
-                        action = ACT_DONE;
-                        stop = true;
-                    }
-                } else {
-                    sgr = 1.0 / sqrt(dgr);
-                }
-                fresh = 0;
+                for (int k = 0; k < P; ++k)
+                    if (k == r) dr = dv[k];
+                utr = clamp_var<F>(r, ur + (fr ? dr : 0.0), H, W);
             }
-            if (!stop) {
-                double m[P], l[P];
+            if (row) s.un[r] = utr;
+            if (lane == 0) s.damped = (ok ? 1 : 0) | (conv ? 2 : 0);
+        }
+        __syncthreads();
+        return;
+    }
+    if (step && fresh) {
+        double m[P], l[P];
 #pragma unroll
-                for (int k = 0; k < P; ++k) m[k] = a[k] + (k == r ? lambda * dgr : 0.0);
-                if (!chol_rows<P>(m, l, lane)) {
-                    lambda *= 10.0;
-                    if (lambda > 1e9) {
-                        status = GM_ST_STALLED;
-                        action = ACT_DONE;
-                    } else {
-                        action = ACT_RETRY;
-                    }
-                } else {
-                    double dv[P];
-                    chol_solve_rows<P>(l, gv, dv);
-                    bool conv = false;
-                    if (!apd) {
-                        double smax = 0.0;
+        for (int k = 0; k < P; ++k) m[k] = a[k];
+        apd = chol_rows<P>(m, l, lane) ? 1 : 0;
+        if (apd) {
+            double dv[P];
+            sgr = sqrt(chol_inv_diag_lane<P>(l, lane));
+            chol_solve_rows<P>(l, gv, dv);
+            double dr = 0.0, smax = 0.0;
 #pragma unroll
-                        for (int k = 0; k < P; ++k) {
-                            const double q = fabs(dv[k]) / lane_value(sgr, k);
-                            if (!(q <= smax)) smax = q;
-                        }
-                        conv = smax < fa.tol;
-                    }
-                    if (conv) {
-                        t -= 1;
-                        status = GM_ST_CONVERGED;
-                        action = ACT_DONE;
-                    } else {
-                        double dr = 0.0;
+            for (int k = 0; k < P; ++k)
+                if (k == lane) dr = dv[k];
+            const double ratio = fabs(dr) / sgr;
 #pragma unroll
-                        for (int k = 0; k < P; ++k)
-                            if (k == r) dr = dv[k];
-                        utr = clamp_var<F>(r, ur + (fr ? dr : 0.0), H, W);
-                        proposed = true;
-                        action = ACT_EVAL;
-                    }
-                }
+            for (int k = 0; k < P; ++k) {
+                const double q = lane_value(ratio, k);
+                if (!(q <= smax)) smax = q;
             }
+            if (smax < fa.tol) {
+                t -= 1;
+                status = GM_ST_CONVERGED;
+                action = ACT_DONE;
+                stop = true;
+            }
+        } else {
+            sgr = 1.0 / sqrt(dgr);
+        }
+        fresh = 0;
+    }
+    __syncthreads();
+    bool proposed = false;
+    if (step && !stop) {
+        const int damped = uniform(s.damped);
+        if (!(damped & 1)) {
+            lambda *= 10.0;
+            if (lambda > 1e9) {
+                status = GM_ST_STALLED;
+                action = ACT_DONE;
+            } else {
+                action = ACT_RETRY;
+            }
+        } else if (!apd && (damped & 2)) {
+            t -= 1;
+            status = GM_ST_CONVERGED;
+            action = ACT_DONE;
+        } else {
+            utr = s.un[r];
+            proposed = true;
+            action = ACT_EVAL;
         }
     }
     if (row) {
@@ -2199,7 +2241,7 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
                     ++epoch;
                 }
             }
-            if (!member && tid < 64) lm_step_wave<F>(s, fa, me.h, me.w);
+            if (!member) lm_step<F>(s, fa, me.h, me.w);
             __syncthreads();
         }
         if (helper) break;
