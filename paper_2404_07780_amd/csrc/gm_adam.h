@@ -30,7 +30,7 @@ __device__ void evaluate_grad(const double *u, const ModelArgs &ma, const BatchA
 {
     constexpr int P = F::P;
     constexpr int NR = 1 + P;
-    const int H = me.h, W = me.w, K = me.k;
+    const int H = me.h, W = me.w, K = KT > 0 ? KT : me.k;
     const int tid = threadIdx.x;
     eval_prologue<F>(u, ma, H, W, sh, planes);
     const cfloat *psf = (const cfloat *)(ba.psf + uniform64(me.psf_off));
@@ -101,16 +101,21 @@ __device__ void evaluate_grad(const double *u, const ModelArgs &ma, const BatchA
             __syncthreads();
             const int i = ti0 + r;
             if (i >= H) continue;
+#pragma unroll 1
+            for (int t = 0; t < 4; t += 2) {
+                const int j0 = tj0 + 4 * cg + t;
+                const int ii[2] = {i, i}, jj[2] = {j0, j0 + 1};
+                double v0[2];
+                float dp[2][F::NPL - 1];
+                planes_at<F, false, FORM_ROW, 2>(sh, ii, jj, H, v0, dp);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int j = tj0 + 4 * cg + t;
-                if (j >= W) continue;
-                double v0;
-                float dp[F::NPL - 1];
-                planes_at<F, false>(sh, i, j, H, v0, dp);
+                for (int n = 0; n < 2; ++n) {
+                    if (j0 + n >= W) continue;
+                    const float q = n == 0 ? (t == 0 ? q4[0] : q4[2]) : (t == 0 ? q4[1] : q4[3]);
 #pragma unroll
-                for (int k = 0; k < P; ++k)
-                    if (!F::analytic(k) && k != F::DER) red[k] = fmaf(q4[t], dp[F::plane(k) - 1], red[k]);
+                    for (int k = 0; k < P; ++k)
+                        if (!F::analytic(k) && k != F::DER) red[k] = fmaf(q, dp[n][F::plane(k) - 1], red[k]);
+                }
             }
         }
     }

@@ -361,14 +361,24 @@ struct Pt {
     float Xf, Yf, r2f, gmask;
 };
 
-template <bool F64>
+// The rotation's roundings are written out: which of two products is fused
+// with the sum is otherwise the compiler's choice, which differs with the code
+// around, and fits that follow a flat valley part at the last bit.
+enum { FORM_POINT = 0, FORM_ROW = 1, FORM_LIGHT = 2 };     // region points; points along a row; light alone
+template <int FORM, typename T>
+__device__ inline void rotate(T c, T s, T dx, T dy, T &X, T &Y)
+{
+    X = FORM == FORM_LIGHT ? fma(s, dy, c * dx) : fma(c, dx, s * dy);
+    Y = FORM == FORM_ROW ? fma(-s, dx, c * dy) : fma(c, dy, -(s * dx));
+}
+
+template <bool F64, int FORM>
 __device__ inline Pt<F64> frame(const Geo &g, double dx, double dy)
 {
     Pt<F64> p;
     if constexpr (F64) {
-        p.X = g.c * dx + g.s * dy;
-        p.Y = -g.s * dx + g.c * dy;
-        p.r2 = p.X * p.X + p.Y * p.Y * g.iq2;
+        rotate<FORM, double>(g.c, g.s, dx, dy, p.X, p.Y);
+        p.r2 = fma(p.X, p.X, p.Y * p.Y * g.iq2);
         p.gmask = 1.0f;
         if (p.r2 < 1e-12) {       // cusp floor r^2 >= 1e-12 px^2: geometry derivatives vanish
             p.r2 = 1e-12;
@@ -379,9 +389,8 @@ __device__ inline Pt<F64> frame(const Geo &g, double dx, double dy)
         p.r2f = (float)p.r2;
     } else {
         float dxf = (float)dx, dyf = (float)dy;
-        p.Xf = g.cf * dxf + g.sf * dyf;
-        p.Yf = -g.sf * dxf + g.cf * dyf;
-        p.r2f = p.Xf * p.Xf + p.Yf * p.Yf * g.iq2f;
+        rotate<FORM, float>(g.cf, g.sf, dxf, dyf, p.Xf, p.Yf);
+        p.r2f = fmaf(p.Xf, p.Xf, p.Yf * p.Yf * g.iq2f);
         p.gmask = 1.0f;
         if (p.r2f < 1e-12f) {
             p.r2f = 1e-12f;
@@ -413,7 +422,7 @@ __device__ inline float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 // prep(us, cst, ..., pre) of one wave from its slot values us (u-space) and
 // shape constants cst -- preceded, where PARTS, by a step in which every wave
 // w makes its share parts(us, ..., w, lane, pre) of Pre (LDS) --
-// a point evaluation pt<F64>(k, dx, dy, I, d) of the light I (FP64 if F64)
+// a point evaluation pt<F64, FORM>(k, dx, dy, I, d) of the light I (FP64 if F64)
 // and its FP32 derivatives d[s] = dI/du_s, and the moment-based start values.
 
 // Sersic (Sec. 4.1): I = I_e exp(-b [(r/r_e)^(1/n) - 1]),
@@ -424,6 +433,7 @@ struct Sersic {
         double lnIe, b, inv2n, lnre2, lnIe2, b2, l2re2;
         float bf, inv2nf, l2re2f, lnIe2f, b2f, bnf, cnf, nbpf, bl2nf;
     };
+    static constexpr int ILP = 2;
     static constexpr int NS = 7, IQ = 5, ITH = 6, IS0 = 3, IS1 = -1;
     __host__ __device__ static constexpr int kind(int s)
     {
@@ -498,10 +508,10 @@ struct Sersic {
         k.nbpf = (float)(n * bp);
         k.bl2nf = (float)(b * kLn2 / (2.0 * n));
     }
-    template <bool F64>
+    template <bool F64, int FORM>
     __device__ static void pt(const K &k, double dx, double dy, double &I64, float *d)
     {
-        Pt<F64> p = frame<F64>(k.g, dx, dy);
+        Pt<F64> p = frame<F64, FORM>(k.g, dx, dy);
         float I, z, L2;
         if constexpr (F64) {
             const double L2d = log2_pt(p.r2) - k.l2re2;      // log2(r^2 / r_e^2)
@@ -551,6 +561,7 @@ struct SersicBox {
         double c, ic, iq;
         float cf, icf, dlrboxf;
     };
+    static constexpr int ILP = 1;
     static constexpr int NS = 8, IQ = 5, ITH = 6, IS0 = 3, IS1 = -1;
     __host__ __device__ static constexpr int kind(int s) { return s == 7 ? KBOX : Sersic::kind(s); }
     static constexpr bool PARTS = true;
@@ -575,13 +586,14 @@ struct SersicBox {
         k.icf = (float)ic;
         k.dlrboxf = (float)(ic + 2.0 * (digamma(ic) - digamma(2.0 * ic)) * ic * ic);
     }
-    template <bool F64>
+    template <bool F64, int FORM>
     __device__ static void pt(const K &k, double dx, double dy, double &I64, float *d)
     {
         const Geo &g = k.g;
         float I, z, L2, Xf, Yf, lx, ly, lq, lc, gmask = 1.0f;
         if constexpr (F64) {
-            const double X = g.c * dx + g.s * dy, Y = -g.s * dx + g.c * dy;
+            double X, Y;
+            rotate<FORM, double>(g.c, g.s, dx, dy, X, Y);
             const double ax = fabs(X), ay = fabs(Y) * k.iq;
             const double la = log(ax), lb = log(ay);
             const double A = exp(k.c * la), Bq = exp(k.c * lb), S = A + Bq;
@@ -605,8 +617,7 @@ struct SersicBox {
             lc = (float)(-lS * k.ic * k.ic + ((ax > 0.0 ? A * la : 0.0) + (ay > 0.0 ? Bq * lb : 0.0)) * k.ic / S);
         } else {
             const float dxf = (float)dx, dyf = (float)dy;
-            Xf = g.cf * dxf + g.sf * dyf;
-            Yf = -g.sf * dxf + g.cf * dyf;
+            rotate<FORM, float>(g.cf, g.sf, dxf, dyf, Xf, Yf);
             const float ax = fabsf(Xf), ay = fabsf(Yf) * g.iqf;
             const float la2 = __log2f(ax), lb2 = __log2f(ay);
             const float A = exp2f(k.cf * la2), Bq = exp2f(k.cf * lb2), S = A + Bq;
@@ -651,6 +662,7 @@ struct ExpDisk {
         double lnI0, irs;
         float lnI02f, irsf, irs2f;
     };
+    static constexpr int ILP = 2;
     static constexpr int NS = 6, IQ = 4, ITH = 5, IS0 = 3, IS1 = -1;
     __host__ __device__ static constexpr int kind(int s)
     {
@@ -669,10 +681,10 @@ struct ExpDisk {
         k.irsf = (float)k.irs;
         k.irs2f = (float)(k.irs * kLog2e);
     }
-    template <bool F64>
+    template <bool F64, int FORM>
     __device__ static void pt(const K &k, double dx, double dy, double &I64, float *d)
     {
-        Pt<F64> p = frame<F64>(k.g, dx, dy);
+        Pt<F64> p = frame<F64, FORM>(k.g, dx, dy);
         float I, r;
         if constexpr (F64) {
             double rd = sqrt(p.r2);
@@ -710,6 +722,7 @@ struct Ferrer {
         double lnI0, a, e2, lnro2;          // e2 = (2 - b) / 2
         float af, ef, iro2f;
     };
+    static constexpr int ILP = 2;
     static constexpr int NS = 6, IQ = 4, ITH = 5, IS0 = 3, IS1 = -1;
     __host__ __device__ static constexpr int kind(int s) { return ExpDisk::kind(s); }
     static constexpr bool PARTS = false;
@@ -728,10 +741,10 @@ struct Ferrer {
         k.ef = (float)(2.0 - bb);
         k.iro2f = (float)exp(-2.0 * lnro);
     }
-    template <bool F64>
+    template <bool F64, int FORM>
     __device__ static void pt(const K &k, double dx, double dy, double &I64, float *d)
     {
-        Pt<F64> p = frame<F64>(k.g, dx, dy);
+        Pt<F64> p = frame<F64, FORM>(k.g, dx, dy);
         float I, u, omu;
         if constexpr (F64) {
             double lnu = k.e2 * (log(p.r2) - k.lnro2);     // ln (r/r_out)^(2-b)
@@ -785,6 +798,7 @@ struct King {
         double I0, al, ial, irc2, A, rt2;
         float I0f, alf, ialf, irc2f, Af, dA_rcf, rt2f;
     };
+    static constexpr int ILP = 2;
     static constexpr int NS = 7, IQ = 5, ITH = 6, IS0 = 3, IS1 = 4;
     __host__ __device__ static constexpr int kind(int s)
     {
@@ -813,10 +827,10 @@ struct King {
         k.dA_rcf = (float)(2.0 * k.A * (T - 1.0) / (al * T));     // dA / d ln r_c
         k.rt2f = (float)k.rt2;
     }
-    template <bool F64>
+    template <bool F64, int FORM>
     __device__ static void pt(const K &k, double dx, double dy, double &I64, float *d)
     {
-        Pt<F64> p = frame<F64>(k.g, dx, dy);
+        Pt<F64> p = frame<F64, FORM>(k.g, dx, dy);
         float shape, s, S, D;
         if constexpr (F64) {
             if (p.r2 >= k.rt2) {
@@ -875,6 +889,7 @@ struct FerrerFree {
     struct K : Ferrer::K {
         float dlaf, dlbf;
     };
+    static constexpr int ILP = 2;
     static constexpr int NS = 8, IQ = 4, ITH = 5, IS0 = 3, IS1 = -1;
     __host__ __device__ static constexpr int kind(int s) { return s == 6 ? KFA : s == 7 ? KFB : Ferrer::kind(s); }
     static constexpr bool PARTS = false;
@@ -887,10 +902,10 @@ struct FerrerFree {
         k.dlaf = (float)(-1.0 / a - (digamma(a) - digamma(a + c2)));
         k.dlbf = (float)(-2.0 * (digamma(c2) - digamma(a + c2)) / ((2.0 - bb) * (2.0 - bb)));
     }
-    template <bool F64>
+    template <bool F64, int FORM>
     __device__ static void pt(const K &k, double dx, double dy, double &I64, float *d)
     {
-        Pt<F64> p = frame<F64>(k.g, dx, dy);
+        Pt<F64> p = frame<F64, FORM>(k.g, dx, dy);
         float I, u, omu, lnuf, lomu;
         if constexpr (F64) {
             double lnu = k.e2 * (log(p.r2) - k.lnro2);     // ln (r/r_out)^(2-b)
@@ -949,6 +964,7 @@ struct KingFree {
     struct K : King::K {
         float lnTf;
     };
+    static constexpr int ILP = 2;
     static constexpr int NS = 8, IQ = 5, ITH = 6, IS0 = 3, IS1 = 4;
     __host__ __device__ static constexpr int kind(int s) { return s == 7 ? KKAL : King::kind(s); }
     static constexpr bool PARTS = false;
@@ -959,10 +975,10 @@ struct KingFree {
         King::prep(u, al, m0, H, W, osf, osw, lane, k);
         k.lnTf = (float)log(1.0 + exp(2.0 * (u[4] - u[3])));
     }
-    template <bool F64>
+    template <bool F64, int FORM>
     __device__ static void pt(const K &k, double dx, double dy, double &I64, float *d)
     {
-        Pt<F64> p = frame<F64>(k.g, dx, dy);
+        Pt<F64> p = frame<F64, FORM>(k.g, dx, dy);
         float shape, s, S, D, lns, lDA;
         if constexpr (F64) {
             if (p.r2 >= k.rt2) {
@@ -1027,6 +1043,7 @@ struct Gaussian {
         double I0, i2s2;
         float I0f, i2s2f;
     };
+    static constexpr int ILP = 2;
     static constexpr int NS = 6, IQ = 4, ITH = 5, IS0 = 3, IS1 = -1;
     __host__ __device__ static constexpr int kind(int s)
     {
@@ -1042,10 +1059,10 @@ struct Gaussian {
         k.I0f = (float)u[2];
         k.i2s2f = (float)k.i2s2;
     }
-    template <bool F64>
+    template <bool F64, int FORM>
     __device__ static void pt(const K &k, double dx, double dy, double &I64, float *d)
     {
-        Pt<F64> p = frame<F64>(k.g, dx, dy);
+        Pt<F64> p = frame<F64, FORM>(k.g, dx, dy);
         float shape;
         if constexpr (F64) {
             double shd = exp(-p.r2 * k.i2s2);
@@ -1081,6 +1098,7 @@ struct Moffat {
         double lnI0, be, ird2;
         float bef, ird2f, rd2f;
     };
+    static constexpr int ILP = 2;
     static constexpr int NS = 6, IQ = 4, ITH = 5, IS0 = 3, IS1 = -1;
     __host__ __device__ static constexpr int kind(int s) { return ExpDisk::kind(s); }
     static constexpr bool PARTS = false;
@@ -1097,10 +1115,10 @@ struct Moffat {
         k.ird2f = (float)k.ird2;
         k.rd2f = (float)(rd * rd);
     }
-    template <bool F64>
+    template <bool F64, int FORM>
     __device__ static void pt(const K &k, double dx, double dy, double &I64, float *d)
     {
-        Pt<F64> p = frame<F64>(k.g, dx, dy);
+        Pt<F64> p = frame<F64, FORM>(k.g, dx, dy);
         float I;
         if constexpr (F64) {
             I64 = exp(k.lnI0 - k.be * log1p(p.r2 * k.ird2));
@@ -1143,8 +1161,12 @@ struct Moffat {
 // One radial component and a flat sky, or (TILT) the tilted-plane sky of
 // Appendix D, eq. (new_sky_I): sky + kx (x - W/2) + ky (y - H/2), whose two
 // gradient variables follow the sky in the LM vector.
+// ILP: profile points a thread evaluates side by side (two hide much of the
+// FP64 latency of one workgroup per CU: 12.5k -> 9.9k cycles per tile; the
+// boxy profile and the pairs, whose points are twice as long, take one).
 template <class C, bool TILT = false>
 struct FamSingle {
+    static constexpr int ILP = C::ILP;
     static constexpr int P = C::NS + (TILT ? 3 : 1), NCOMP = 1, NRAD = 1, SKY = C::NS, ND = C::NS;
     static constexpr int DER = C::kind(2) == KMAG ? 2 : -1;
     static constexpr int NPL = 1 + C::NS - (DER >= 0 ? 1 : 0);
@@ -1204,10 +1226,10 @@ struct FamSingle {
         else return p.sky;
     }
     __device__ static const Geo &geo(const Prep &p, int) { return p.k0.g; }
-    template <bool F64>
+    template <bool F64, int FORM>
     __device__ static void comp_pt(const Prep &p, int, double dx, double dy, double &I, float *d)
     {
-        C::template pt<F64>(p.k0, dx, dy, I, d);
+        C::template pt<F64, FORM>(p.k0, dx, dy, I, d);
     }
     // component derivatives into the derivative planes (index = plane - 1)
     __device__ static void scatter(int, const float *d, float *dp)
@@ -1235,6 +1257,7 @@ struct FamSingle {
 // cst[0..1], C2's at cst[2..3].
 template <class C1, class C2>
 struct FamPair {
+    static constexpr int ILP = 1;
     static constexpr int O2 = C1::NS - 2;                  // C2 slot s >= 2 sits at u[O2 + s]
     static constexpr int P = C1::NS + C2::NS - 2 + 1, NCOMP = 2, NRAD = 2, SKY = P - 1;
     static constexpr int ND = C1::NS > C2::NS ? C1::NS : C2::NS;
@@ -1280,11 +1303,11 @@ struct FamPair {
     }
     __device__ static double sky_at(const Prep &p, double, double) { return p.sky; }
     __device__ static const Geo &geo(const Prep &p, int c) { return c == 0 ? p.k0.g : p.k1.g; }
-    template <bool F64>
+    template <bool F64, int FORM>
     __device__ static void comp_pt(const Prep &p, int c, double dx, double dy, double &I, float *d)
     {
-        if (c == 0) C1::template pt<F64>(p.k0, dx, dy, I, d);
-        else C2::template pt<F64>(p.k1, dx, dy, I, d);
+        if (c == 0) C1::template pt<F64, FORM>(p.k0, dx, dy, I, d);
+        else C2::template pt<F64, FORM>(p.k1, dx, dy, I, d);
     }
     __device__ static void scatter(int c, const float *d, float *dp)
     {

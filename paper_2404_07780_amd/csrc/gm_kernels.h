@@ -238,11 +238,30 @@ __device__ void eval_prologue(const double *u, const ModelArgs &ma, int H, int W
 #pragma unroll
             for (int q = 0; q < F::ND; ++q) ad[q] = 0.0f;
             const double dy = ((double)(H - i) - ((double)t + 0.5) * invf) - g.y0;
-            for (int s = 0; s < f; ++s) {
+            // ILP samples side by side, added in order (no branch between a
+            // sample's products and its sums, which the compiler contracts)
+            int s = 0;
+#pragma unroll 1
+            for (; s + F::ILP <= f; s += F::ILP) {
+                double I[F::ILP];
+                float d[F::ILP][F::ND] = {};
+#pragma unroll
+                for (int n = 0; n < F::ILP; ++n) {
+                    const double dx = ((double)j + ((double)(s + n) + 0.5) * invf) - g.x0;
+                    F::template comp_pt<true, FORM_ROW>(sh.prep, c, dx, dy, I[n], d[n]);
+                }
+#pragma unroll
+                for (int n = 0; n < F::ILP; ++n) {
+                    aI += I[n];
+#pragma unroll
+                    for (int q = 0; q < F::ND; ++q) ad[q] += d[n][q];
+                }
+            }
+            if (F::ILP > 1 && s < f) {
                 const double dx = ((double)j + ((double)s + 0.5) * invf) - g.x0;
                 double I;
                 float d[F::ND] = {};
-                F::template comp_pt<true>(sh.prep, c, dx, dy, I, d);
+                F::template comp_pt<true, FORM_ROW>(sh.prep, c, dx, dy, I, d);
                 aI += I;
 #pragma unroll
                 for (int q = 0; q < F::ND; ++q) ad[q] += d[q];
@@ -253,13 +272,17 @@ __device__ void eval_prologue(const double *u, const ModelArgs &ma, int H, int W
         }
         __syncthreads();
         const double norm = 1.0 / (double)(f * f);
-        for (int pix = tid; pix < nwin; pix += NT) {
-            double s0 = 0.0;
-            for (int t = 0; t < f; ++t) s0 += sd[pix * f + t];
-            sh.win0[c][pix] = s0 * norm;
-#pragma unroll
-            for (int q = 0; q < F::ND; ++q) {
+        // each thread sums one quantity of one pixel over its sub-rows
+        for (int it = tid; it < nwin * (F::ND + 1); it += NT) {
+            const int pix = it / (F::ND + 1), q = it - pix * (F::ND + 1);
+            if (q == F::ND) {
+                double s0 = 0.0;
+#pragma unroll 4
+                for (int t = 0; t < f; ++t) s0 += sd[pix * f + t];
+                sh.win0[c][pix] = s0 * norm;
+            } else {
                 float s = 0.0f;
+#pragma unroll 4
                 for (int t = 0; t < f; ++t) s += sf[(pix * f + t) * F::ND + q];
                 sh.win[c][pix][q] = s * (float)norm;
             }
@@ -269,30 +292,45 @@ __device__ void eval_prologue(const double *u, const ModelArgs &ma, int H, int W
 }
 
 // Light (FP64 if F64) and derivative planes (dp[q - 1] for plane q) of the
-// convolved components at pixel (i, j).
-template <class F, bool F64>
-__device__ inline void planes_at(const EvalShared<F> &sh, int i, int j, int H, double &v0, float *dp)
+// convolved components at the N pixels (i[n], j[n]).  The profile is evaluated
+// at every pixel first, N independent chains of FP64 arithmetic side by side,
+// and the pixels of the oversampled window then take the table's values.
+template <class F, bool F64, int FORM, int N>
+__device__ inline void planes_at(const EvalShared<F> &sh, const int (&i)[N], const int (&j)[N], int H,
+                                 double (&v0)[N], float (&dp)[N][F::NPL - 1])
 {
-    v0 = 0.0;
 #pragma unroll
-    for (int q = 0; q < F::NPL - 1; ++q) dp[q] = 0.0f;
+    for (int n = 0; n < N; ++n) {
+        v0[n] = 0.0;
+#pragma unroll
+        for (int q = 0; q < F::NPL - 1; ++q) dp[n][q] = 0.0f;
+    }
 #pragma unroll
     for (int c = 0; c < F::NCOMP; ++c) {
         const Geo &g = F::geo(sh.prep, c);
-        double I;
-        float d[F::ND] = {};
-        if (i >= g.wi0 && i <= g.wi1 && j >= g.wj0 && j <= g.wj1) {
-            const int pix = (i - g.wi0) * (g.wj1 - g.wj0 + 1) + (j - g.wj0);
-            I = sh.win0[c][pix];
+        double I[N];
+        float d[N][F::ND] = {};
+        auto point = [&](int n) {
+            const double dx = ((double)j[n] + 0.5) - g.x0;
+            const double dy = ((double)(H - i[n]) - 0.5) - g.y0;
+            F::template comp_pt<F64, FORM>(sh.prep, c, dx, dy, I[n], d[n]);
+        };
+        if (N > 1)
 #pragma unroll
-            for (int q = 0; q < F::ND; ++q) d[q] = sh.win[c][pix][q];
-        } else {
-            const double dx = ((double)j + 0.5) - g.x0;
-            const double dy = ((double)(H - i) - 0.5) - g.y0;
-            F::template comp_pt<F64>(sh.prep, c, dx, dy, I, d);
+            for (int n = 0; n < N; ++n) point(n);
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            if (i[n] >= g.wi0 && i[n] <= g.wi1 && j[n] >= g.wj0 && j[n] <= g.wj1) {
+                const int pix = (i[n] - g.wi0) * (g.wj1 - g.wj0 + 1) + (j[n] - g.wj0);
+                I[n] = sh.win0[c][pix];
+#pragma unroll
+                for (int q = 0; q < F::ND; ++q) d[n][q] = sh.win[c][pix][q];
+            } else if (N == 1) {
+                point(n);
+            }
+            v0[n] += I[n];
+            F::scatter(c, d[n], dp[n]);
         }
-        v0 += I;
-        F::scatter(c, d, dp);
     }
 }
 
@@ -302,7 +340,7 @@ __device__ inline void planes_at(const EvalShared<F> &sh, int i, int j, int H, d
 // convolution's zero padding; the points inside form a rectangle whose
 // profile values are spread linearly over all threads of the workgroup.
 template <class F, int LO, int HI, bool SH = false>
-__device__ void fill_region(const EvalShared<F> &sh, float *buf, int H, int W, int K, int ti0, int tj0)
+__device__ inline void fill_region(const EvalShared<F> &sh, float *buf, int H, int W, int K, int ti0, int tj0)
 {
     const int IH = region_h(K), IWP = region_wp(K), IW = TILE + K - 1, c = (K - 1) / 2;
     const int plane_sz = IH * IWP;
@@ -334,12 +372,26 @@ __device__ void fill_region(const EvalShared<F> &sh, float *buf, int H, int W, i
     // row count (< 2^8) and at least 1/(2 nc) > 2^-9 away from an integer,
     // while the float rounding moves it by less than 2^-14
     const float rnc = 1.0f / (float)nc;
-    for (int t = threadIdx.x; t < npts; t += NT) {
-        const int rr = (int)(((float)t + 0.5f) * rnc), ri = r0 + rr, ci = c0 + (t - rr * nc);
-        double v0;
-        float dp[F::NPL - 1];
-        planes_at<F, LO == 0>(sh, ti0 - c + ri, tj0 - c + ci, H, v0, dp);
-        store(ri, ci, v0, dp);
+    // N points per thread and step (the last step's second may be none)
+    constexpr int N = F::ILP, FORM = LO == 0 && HI == 1 ? FORM_LIGHT : FORM_POINT;
+#pragma unroll 1
+    for (int t = threadIdx.x; t < npts; t += N * NT) {
+        int ri[N], ci[N], i[N], j[N];
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            const int tn = n ? min(t + n * NT, npts - 1) : t;
+            const int rr = (int)(((float)tn + 0.5f) * rnc);
+            ri[n] = r0 + rr;
+            ci[n] = c0 + (tn - rr * nc);
+            i[n] = ti0 - c + ri[n];
+            j[n] = tj0 - c + ci[n];
+        }
+        double v0[N];
+        float dp[N][F::NPL - 1];
+        planes_at<F, LO == 0, FORM, N>(sh, i, j, H, v0, dp);
+#pragma unroll
+        for (int n = 0; n < N; ++n)
+            if (n == 0 || t + n * NT < npts) store(ri[n], ci[n], v0[n], dp[n]);
     }
 }
 
@@ -1219,7 +1271,7 @@ __device__ void evaluate(const double *u, const ModelArgs &ma, const BatchArgs &
 {
     constexpr int P = F::P;
     constexpr int NR = 1 + P + P * (P + 1) / 2;
-    const int H = me.h, W = me.w, K = me.k;
+    const int H = me.h, W = me.w, K = KT > 0 ? KT : me.k;
     const int tid = threadIdx.x;
     const int nty = (H + TILE - 1) / TILE, ntx = (W + TILE - 1) / TILE;
     const int ntiles = nty * ntx;
@@ -2362,7 +2414,7 @@ __global__ __launch_bounds__(NT, 2) void image_kernel(ModelArgs ma, BatchArgs ba
         const TileItem ti = ia.tiles[it];
         const int g = uniform(ti.gal);
         const Meta me = ba.meta[g];
-        const int H = me.h, W = me.w, K = me.k;
+        const int H = me.h, W = me.w, K = KT > 0 ? KT : me.k;
         if (tid == 0) {
             const double *pp = ia.params + (int64_t)g * ma.p;
             for (int k = 0; k < P; ++k) {
