@@ -807,23 +807,82 @@ __device__ inline void conv_any(const float *p, int K, int IWP, const float *psl
     hi = a1;
 }
 
-// The FP64 light plane with PSF sides above 15: each row in two halves of
-// taps, each with only the part of the segment it reads (taps v < VS read
-// elements from ES on), the taps as scalar loads.
+// Order products before the reads that follow, as keep_order.
+__device__ inline void keep_order64(double (&a)[4])
+{
+    asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3])::"memory");
+}
+
+// Segment elements E0 .. E0 + N - 1 that taps V0 .. V1-1 of a row meet.
+template <int KT, int V0, int V1, int E0>
+struct Part64 {
+    static constexpr int N = ((KT + 2 - V0) - E0 + 2) / 2 * 2;
+    double seg[N];
+    __device__ inline void load(const double *rp)
+    {
+        const double2 *vp = reinterpret_cast<const double2 *>(rp + E0);
+#pragma unroll
+        for (int q = 0; q < N / 2; ++q) {
+            const double2 t = vp[q];
+            seg[2 * q] = t.x;
+            seg[2 * q + 1] = t.y;
+        }
+    }
+    __device__ inline void add(const float *tp, double (&a)[4]) const
+    {
+#pragma unroll
+        for (int v = V0; v < V1; ++v) {
+            const double pv = (double)tp[v];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) a[t] = fma(pv, seg[KT - 1 - v + t - E0], a[t]);
+        }
+        keep_order64(a);
+    }
+};
+
+// The FP64 light plane with PSF sides above 15, the taps as scalar loads, each
+// row in two halves of taps (v < VS meet elements from ES on, v >= VS elements
+// from 0).  Scalar loads and LDS reads share one counter and complete out of
+// order with each other, so a wait between them is a wait for all: each half's
+// reads (the second half's with the next row's taps) are issued in front of
+// the other half's products and waited for behind them.  Bound by the FP64
+// units (100 FMAs and 25 conversions a row at side 25): 21.5k cycles per tile
+// with waits in front of each half, now 19.2k; with the taps from LDS 23k, with
+// whole rows ahead the registers spill.
 template <int KT>
 __device__ inline void conv64_wide(const double *b64, const cfloat *psf, int r, double (&acc0)[4])
 {
     constexpr int IWP = (28 + 4 * ((KT + 3 + 3) / 4));
     constexpr int ES = 4 * ((KT - 1) / 8), VS = KT - ES;
-    double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;
+    Part64<KT, 0, VS, ES> a;
+    Part64<KT, VS, KT, 0> b;
+    double d[4] = {0.0, 0.0, 0.0, 0.0};
+    float ta[KT], tb[KT];
+    const double *rp = b64 + (r + KT - 1) * IWP;
+    auto taps = [&](int u, float (&t)[KT]) {
+#pragma unroll
+        for (int v = 0; v < KT; ++v) t[v] = psf[u * KT + v];
+    };
+    taps(0, ta);
+    a.load(rp);
 #pragma unroll 1
-    for (int u = 0; u < KT; ++u) {
-        const int ro = (r + KT - 1 - u) * IWP;
-        const cfloat *pr = psf + u * KT;
-        row_part<KT, 0, VS, ES>(b64 + ro, pr, d0, d1, d2, d3);
-        row_part<KT, VS, KT, 0>(b64 + ro, pr, d0, d1, d2, d3);
+    for (int u = 0; u + 1 < KT; u += 2) {
+        b.load(rp - u * IWP);
+        a.add(ta, d);
+        a.load(rp - (u + 1) * IWP);
+        taps(u + 1, tb);
+        b.add(ta, d);
+        b.load(rp - (u + 1) * IWP);
+        a.add(tb, d);
+        a.load(rp - (u + 2) * IWP);
+        taps(u + 2, ta);
+        b.add(tb, d);
     }
-    acc0[0] = d0; acc0[1] = d1; acc0[2] = d2; acc0[3] = d3;
+    b.load(rp - (KT - 1) * IWP);
+    a.add(ta, d);
+    b.add(ta, d);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc0[t] = d[t];
 }
 
 // The FP64 light plane with PSF sides up to 15.  Every load of the loop is an
