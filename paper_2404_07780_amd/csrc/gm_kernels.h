@@ -681,7 +681,7 @@ __device__ inline void conv_pair(const float *p, const float *psl, f32x4 &lo, f3
 
 // Two plane pairs at once (p and q as conv_pair's p): four accumulators in
 // turn, so that no instruction waits for the one two before it (a pair alone
-// needs a wait state on every third): 16,384 one-tile Sersic fits 43.6 -> 41.9 ms.
+// needs a wait state on every third): 16,384 Sersic fits of 64 x 64 43.6 -> 41.9 ms.
 template <int X>
 __device__ inline void mfma_row4(const float *t1, const float *t0, const float *s, const float *z, f32x4 (&a)[4])
 {
@@ -2700,7 +2700,87 @@ __device__ inline void moment_pixels(const BatchArgs &ba, int64_t off, int q0, i
     }
 }
 
-__device__ inline Moments image_moments(const BatchArgs &ba, const Meta &me, double m0, double *sred)
+// A cutout of at most kMomPix pixels is read from memory once: each thread
+// keeps its pixels (data, sigma, and a bit each for ok) in registers over the
+// three passes (16,384 cutouts of 64 x 64: the guess 364 -> 267 us; more pixels
+// than these leave too few workgroups per CU).  Bound by instruction issue.
+constexpr int kMomB = 4;                              // batches of kMomU pixels per thread
+constexpr int kMomPix = kMomB * kMomU * NT;           // 4096: 64 x 64
+
+struct MomPixels {
+    float d[kMomB * kMomU], s[kMomB * kMomU];
+    uint32_t ok;
+};
+
+__device__ inline void moment_read(const BatchArgs &ba, int64_t off, int npix, MomPixels &px)
+{
+    px.ok = 0;
+#pragma unroll
+    for (int b = 0; b < kMomB; ++b) {
+        float d[kMomU], s[kMomU];
+        bool ok[kMomU];
+        moment_pixels(ba, off, threadIdx.x + b * kMomU * NT, npix, d, s, ok);
+#pragma unroll
+        for (int u = 0; u < kMomU; ++u) {
+            px.d[b * kMomU + u] = d[u];
+            px.s[b * kMomU + u] = s[u];
+            px.ok |= (ok[u] ? 1u : 0u) << (b * kMomU + u);
+        }
+    }
+}
+
+// f(q, d, s, k) for each of this thread's usable pixels q = tid + k NT, k
+// increasing (k: of a cutout whose pixels are kept).  `which`: the bits of the
+// kept pixels it is called for.
+template <bool KEPT, class Fn>
+__device__ inline void moment_each(const BatchArgs &ba, int64_t off, int npix, const MomPixels &px, uint32_t which, Fn f)
+{
+    if constexpr (KEPT) {
+        // each pixel is worked on anew in every pass: what the compiler would
+        // carry over (row, column, FP64 value) costs the second workgroup per CU
+        int t = threadIdx.x;
+#pragma unroll
+        for (int k = 0; k < kMomB * kMomU; ++k) {
+            float d = px.d[k];
+            asm volatile("" : "+v"(t), "+v"(d));
+            if ((which >> k) & 1u) f(t + k * NT, d, px.s[k], k);
+        }
+    } else {
+        for (int q0 = threadIdx.x; q0 < npix; q0 += kMomU * NT) {
+            float d[kMomU], sg[kMomU];
+            bool ok[kMomU];
+            moment_pixels(ba, off, q0, npix, d, sg, ok);
+#pragma unroll
+            for (int u = 0; u < kMomU; ++u)
+                if (ok[u]) f(q0 + u * NT, d[u], sg[u], 0);
+        }
+    }
+}
+
+// Block sums of N values at once, each in block_sum's order; sred: N NWAVE doubles.
+template <int N>
+__device__ inline void block_sums(double (&v)[N], double *sred)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int n = 0; n < N; ++n) v[n] = wave_sum(v[n]);
+    __syncthreads();
+    if (lane == 0)
+#pragma unroll
+        for (int n = 0; n < N; ++n) sred[n * NWAVE + wave] = v[n];
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        double s = sred[n * NWAVE];
+        for (int w = 1; w < NWAVE; ++w) s += sred[n * NWAVE + w];
+        v[n] = s;
+    }
+}
+constexpr int kMomRed = 5 * NWAVE;        // doubles of LDS for image_moments
+
+template <bool KEPT>
+__device__ inline Moments image_moments(const BatchArgs &ba, const Meta &me, double m0, double *sred,
+                                        const MomPixels &px, int tail)
 {
     const int tid = threadIdx.x;
     const int H = me.h, W = me.w;
@@ -2709,85 +2789,70 @@ __device__ inline Moments image_moments(const BatchArgs &ba, const Meta &me, dou
     // rounding of the product moves it by less than 2^-13
     const int npix = H * W;
     const float rW = 1.0f / (float)W;
-    // each thread takes its pixels q = tid + k NT in increasing k, kMomU at a time
-    double ss = 0.0, sc = 0.0;
-    for (int q0 = tid; q0 < npix; q0 += kMomU * NT) {
-        float d[kMomU], sg[kMomU];
-        bool ok[kMomU];
-        moment_pixels(ba, me.img_off, q0, npix, d, sg, ok);
-#pragma unroll
-        for (int u = 0; u < kMomU; ++u) {
-            const int q = q0 + u * NT;
-            const int i = (int)(((float)q + 0.5f) * rW), j = q - i * W;
-            if (ok[u] && (i < 2 || i >= H - 2 || j < 2 || j >= W - 2)) {
-                ss += d[u];
-                sc += 1.0;
-            }
+    auto row_of = [&](int q) { return (int)(((float)q + 0.5f) * rW); };
+    const unsigned hin = max(H - 4, 0), win = max(W - 4, 0);
+    double a2[2] = {0.0, 0.0};
+    int n = 0;
+    moment_each<KEPT>(ba, me.img_off, npix, px, px.ok, [&](int q, float d, float, int) {
+        const int i = row_of(q), j = q - __mul24(i, W);
+        if ((unsigned)(i - 2) >= hin || (unsigned)(j - 2) >= win) {       // the border, two pixels wide
+            a2[0] += d;
+            ++n;
         }
-    }
-    ss = block_sum(ss, sred);
-    sc = block_sum(sc, sred);
+    });
+    a2[1] = n;
+    block_sums<2>(a2, sred);
     Moments mo;
-    mo.sky0 = sc > 0.0 ? ss / sc : 0.0;
-    double f0 = 0.0, fx = 0.0, fy = 0.0, cnt = 0.0, pk = 0.0;
-    for (int q0 = tid; q0 < npix; q0 += kMomU * NT) {
-        float d[kMomU], sg[kMomU];
-        bool ok[kMomU];
-        moment_pixels(ba, me.img_off, q0, npix, d, sg, ok);
-#pragma unroll
-        for (int u = 0; u < kMomU; ++u) {
-            const double dp = (double)d[u] - mo.sky0;
-            if (!ok[u] || !(dp > 3.0 * (double)sg[u])) continue;
-            const int q = q0 + u * NT;
-            const int i = (int)(((float)q + 0.5f) * rW), j = q - i * W;
-            double x = j + 0.5, y = (double)H - i - 0.5;
-            f0 += dp; fx += dp * x; fy += dp * y; cnt += 1.0;
-            pk = fmax(pk, dp);
-        }
-    }
-    f0 = block_sum(f0, sred);
-    fx = block_sum(fx, sred);
-    fy = block_sum(fy, sred);
-    cnt = block_sum(cnt, sred);
-    {   // block max of the peak
+    mo.sky0 = a2[1] > 0.0 ? a2[0] / a2[1] : 0.0;
+    double a4[4] = {0.0, 0.0, 0.0, 0.0}, pk = 0.0;
+    n = 0;
+    uint32_t bright = 0;        // the kept pixels above 3 sigma
+    moment_each<KEPT>(ba, me.img_off, npix, px, px.ok, [&](int q, float d, float s, int k) {
+        const double dp = (double)d - mo.sky0;
+        if (!(dp > 3.0 * (double)s)) return;
+        bright |= 1u << k;
+        const int i = row_of(q), j = q - __mul24(i, W);
+        const double x = j + 0.5, y = (H - i) - 0.5;
+        a4[0] += dp; a4[1] += dp * x; a4[2] += dp * y;
+        ++n;
+        pk = fmax(pk, dp);
+    });
+    a4[3] = n;
+    {   // the peak's block maximum goes through the same barriers
         const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) pk = fmax(pk, __shfl_xor(pk, o, 64));
         __syncthreads();
-        if (lane == 0) sred[wave] = pk;
-        __syncthreads();
-        pk = sred[0];
-        for (int w = 1; w < NWAVE; ++w) pk = fmax(pk, sred[w]);
+        if (lane == 0) sred[4 * NWAVE + wave] = pk;
+        block_sums<4>(a4, sred);
+        pk = sred[4 * NWAVE];
+        for (int w = 1; w < NWAVE; ++w) pk = fmax(pk, sred[4 * NWAVE + w]);
     }
+    const double f0 = a4[0], fx = a4[1], fy = a4[2], cnt = a4[3];
     mo.f0 = f0;
     mo.pk = pk > 0.0 ? pk : 1.0;
     mo.xc = 0.5 * W; mo.yc = 0.5 * H; mo.r0 = 3.0; mo.q0 = 1.0; mo.th0 = 0.0;
     const bool have = cnt >= 5.0 && f0 > 0.0;
-    double mxx = 0.0, myy = 0.0, mxy = 0.0;
+    double a3[3] = {0.0, 0.0, 0.0};
     if (have) {
         mo.xc = fx / f0;
         mo.yc = fy / f0;
-        for (int q0 = tid; q0 < npix; q0 += kMomU * NT) {
-            float d[kMomU], sg[kMomU];
-            bool ok[kMomU];
-            moment_pixels(ba, me.img_off, q0, npix, d, sg, ok);
-#pragma unroll
-            for (int u = 0; u < kMomU; ++u) {
-                const double dp = (double)d[u] - mo.sky0;
-                if (!ok[u] || !(dp > 3.0 * (double)sg[u])) continue;
-                const int q = q0 + u * NT;
-                const int i = (int)(((float)q + 0.5f) * rW), j = q - i * W;
-                double dx = j + 0.5 - mo.xc, dy = (double)H - i - 0.5 - mo.yc;
-                mxx += dp * dx * dx; myy += dp * dy * dy; mxy += dp * dx * dy;
-            }
-        }
+        moment_each<KEPT>(ba, me.img_off, npix, px, bright, [&](int q, float d, float s, int) {
+            const double dp = (double)d - mo.sky0;
+            if (!KEPT && !(dp > 3.0 * (double)s)) return;
+            const int i = row_of(q), j = q - __mul24(i, W);
+            const double dx = j + 0.5 - mo.xc, dy = (H - i) - 0.5 - mo.yc;
+            a3[0] += dp * dx * dx; a3[1] += dp * dy * dy; a3[2] += dp * dx * dy;
+        });
     }
-    mxx = block_sum(mxx, sred);
-    myy = block_sum(myy, sred);
-    mxy = block_sum(mxy, sred);
+    block_sums<3>(a3, sred);
+    if ((tid >> 6) != tail) return mo;
+    double mxx = a3[0], myy = a3[1], mxy = a3[2];
     if (have) {
         mxx /= f0; myy /= f0; mxy /= f0;
-        double tr = 0.5 * (mxx + myy), dd = sqrt(0.25 * (mxx - myy) * (mxx - myy) + mxy * mxy);
+        // which product is fused with the sum is written out, not left to the compiler
+        const double df = mxx - myy;
+        double tr = 0.5 * (mxx + myy), dd = sqrt(fma(df, 0.25 * df, mxy * mxy));
         double lp = tr + dd, lm = fmax(tr - dd, 0.0);
         mo.q0 = lp > 0.0 ? sqrt(lm / lp) : 1.0;
         mo.q0 = fmin(fmax(mo.q0, 0.1), 1.0);
@@ -2797,6 +2862,19 @@ __device__ inline Moments image_moments(const BatchArgs &ba, const Meta &me, dou
     }
     mo.mg = m0 - 2.5 * log10(fmax(f0, 1e-3));
     return mo;
+}
+
+// Moments of a cutout of any size; px is filled where it is kept.  mg, r0, q0
+// and th0 are the work of wave `tail` alone (1,400 instructions with the
+// features'; it alternates from cutout to cutout, so that no SIMD has them all).
+__device__ inline Moments cutout_moments(const BatchArgs &ba, const Meta &me, double m0, double *sred, MomPixels &px,
+                                         int tail)
+{
+    if (me.h * me.w <= kMomPix) {
+        moment_read(ba, me.img_off, me.h * me.w, px);
+        return image_moments<true>(ba, me, m0, sred, px, tail);
+    }
+    return image_moments<false>(ba, me, m0, sred, px, tail);
 }
 
 // The default start of one galaxy from its image moments, written into its
@@ -2814,14 +2892,15 @@ __device__ inline void moments_guess(const ModelArgs &ma, const Moments &mo, dou
 }
 
 template <class F>
-__global__ __launch_bounds__(NT) void guess_kernel(ModelArgs ma, BatchArgs ba, GuessArgs ga)
+__global__ __launch_bounds__(NT, 4) void guess_kernel(ModelArgs ma, BatchArgs ba, GuessArgs ga)
 {
-    __shared__ double sred[NWAVE];
-    const int tid = threadIdx.x;
+    __shared__ double sred[kMomRed];
     for (int g = blockIdx.x; g < ga.n_gal; g += gridDim.x) {
         const Meta me = ba.meta[g];
-        const Moments mo = image_moments(ba, me, ma.m0, sred);
-        if (tid == 0) {
+        const int tail = (g / 256) % NWAVE;
+        MomPixels px;
+        const Moments mo = cutout_moments(ba, me, ma.m0, sred, px, tail);
+        if ((int)threadIdx.x == 64 * tail) {
             if (ga.moments) {
                 double *m6 = ga.moments + (int64_t)g * 6;
                 m6[0] = mo.xc - 0.5 * me.w; m6[1] = mo.yc - 0.5 * me.h; m6[2] = mo.mg;
