@@ -12,10 +12,11 @@
 // FP32 accumulation and fused epilogues: bias + GELU (+ the FP32
 // pre-activation kept for the backward pass), bias only, plain FP32 (weight
 // gradients) and the GELU derivative of the backward pass.  One 256-thread
-// workgroup computes a 64 x 64 output tile; each of its four waves owns a
-// 32 x 32 quarter as 2 x 2 MFMA blocks; operands are staged through LDS in
-// 32-deep K slices, both stored K-contiguous so that every lane fetches its
-// eight BF16 operands with one 16-byte LDS read.
+// workgroup computes a 64 x 64 output tile (weight gradients of large batches:
+// 128 x 128); each of its four waves owns a quarter of it in 16 x 16 MFMA
+// blocks; operands are staged through LDS in 32-deep K slices, both stored
+// K-contiguous so that every lane fetches its eight BF16 operands with one
+// 16-byte LDS read.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -206,66 +207,127 @@ __device__ inline void put(uint16_t *T, const typename PieceOf<RMAJOR>::type &f)
         put_kmajor(T, f);
 }
 
-// C = A B over the K range [kbeg, kend) of this workgroup's split (blockIdx.z
-// of gridDim.z splits, each a whole number of K slices): the splits of an
-// EPI_F32 product write their partial sums to cf + z * M * ldcf, which
-// reduce_splits_kernel adds in split order.
-template <bool AT, bool BT, int EPI>
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g)
+// K slices staged per pair of barriers, for output tiles of 64 T a side: a
+// 64 x 64 tile takes four (its time is the latency of the reads: 4,096 rows
+// forward 62 us with one, 58 with two, 52 with four), a 128 x 128 tile one
+// (46 us of weight gradients with two, 40 with one: the LDS leaves room for
+// more workgroups).
+template <int T>
+__host__ __device__ constexpr int stages()
 {
-    __shared__ __attribute__((aligned(16))) uint16_t As[GT * LDK];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[GT * LDK];
+    return T == 1 ? 4 : 1;
+}
+template <int T>
+__host__ __device__ constexpr int tile_lds()        // BF16 elements of LDS per operand
+{
+    return stages<T>() * T * GT * LDK;
+}
+
+// One tile (bx, by) of C = A B, 64 T a side, over the K range [kbeg, kend) of
+// split bz of nz splits, each a whole number of K slices: the splits of an
+// EPI_F32 product write their partial sums to cf + z * M * ldcf, which
+// reduce_splits_kernel adds in split order.  Each of the four waves owns a
+// quarter as 2 T x 2 T MFMA blocks.  With few tiles the latency of the operand
+// reads is the bound (33 slices for the first layer, 16 for the others): the
+// reads of stages() slices are in flight together behind the products of the
+// slices before.
+template <bool AT, bool BT, int EPI, int T>
+__device__ inline void gemm_tile(const GemmArgs &g, int bx, int by, int bz, int nz, uint16_t *As, uint16_t *Bs)
+{
+    constexpr int GS = stages<T>(), NB = 2 * T;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    const int m0 = by * GT * T, n0 = bx * GT * T;
+    const int wm = (wave >> 1) * 32 * T, wn = (wave & 1) * 32 * T;
     const int lr = lane & 15, lk = 8 * (lane >> 4);
-    const int nsl = (g.K + GK - 1) / GK, per = (nsl + gridDim.z - 1) / gridDim.z;
-    const int kbeg = blockIdx.z * per * GK, kend = min(g.K, kbeg + per * GK);
-    f32x4 acc[2][2];
+    const int nsl = (g.K + GK - 1) / GK, per = (nsl + nz - 1) / nz;
+    const int kbeg = bz * per * GK, kend = min(g.K, kbeg + per * GK);
+    f32x4 acc[NB][NB];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    typename PieceOf<AT>::type fa;
-    typename PieceOf<!BT>::type fb;
+        for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    typename PieceOf<AT>::type fa[GS][T];
+    typename PieceOf<!BT>::type fb[GS][T];
     const int *bmap = BT ? nullptr : g.bmap;
-    if (kbeg < kend) {
-        gather_piece<AT>(fa, g.amap, m0, g.M, kbeg, kend);
-        gather_piece<!BT>(fb, bmap, n0, g.N, kbeg, kend);
-        read_piece<AT>(fa, g.a, g.lda, m0, g.M, kbeg, kend);
-        read_piece<!BT>(fb, g.b, g.ldb, n0, g.N, kbeg, kend);
-    }
-    for (int k0 = kbeg; k0 < kend; k0 += GK) {
-        put<AT>(As, fa);
-        put<!BT>(Bs, fb);
-        __syncthreads();
-        if (k0 + GK < kend) {       // the next slice's global reads overlap this slice's products
-            gather_piece<AT>(fa, g.amap, m0, g.M, k0 + GK, kend);
-            gather_piece<!BT>(fb, bmap, n0, g.N, k0 + GK, kend);
-            read_piece<AT>(fa, g.a, g.lda, m0, g.M, k0 + GK, kend);
-            read_piece<!BT>(fb, g.b, g.ldb, n0, g.N, k0 + GK, kend);
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int s = 0; s < GS; ++s)
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                if (AT) gather_piece<AT>(fa[s][t], g.amap, m0 + t * GT, g.M, k0 + s * GK, kend);
+                if (!BT) gather_piece<!BT>(fb[s][t], bmap, n0 + t * GT, g.N, k0 + s * GK, kend);
+            }
+#pragma unroll
+        for (int s = 0; s < GS; ++s)
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                read_piece<AT>(fa[s][t], g.a, g.lda, m0 + t * GT, g.M, k0 + s * GK, kend);
+                read_piece<!BT>(fb[s][t], g.b, g.ldb, n0 + t * GT, g.N, k0 + s * GK, kend);
+            }
+    };
+#pragma unroll
+    for (int t = 0; t < T; ++t) {       // the rows of a K-contiguous operand stay the same
+        if (!AT) gather_piece<AT>(fa[0][t], g.amap, m0 + t * GT, g.M, 0, kend);
+        if (BT) gather_piece<!BT>(fb[0][t], bmap, n0 + t * GT, g.N, 0, kend);
+#pragma unroll
+        for (int s = 1; s < GS; ++s) {
+            if (!AT) fa[s][t] = fa[0][t];
+            if (BT) fb[s][t] = fb[0][t];
         }
-        bf16x8 af[2], bfr[2];
+    }
+    if (kbeg < kend) fetch(kbeg);
+    float z[EPI == EPI_DGELU ? NB : 1][NB][4];        // the epilogue's operand, read behind the products
+    if constexpr (EPI == EPI_DGELU) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            af[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(&As[(wm + 16 * i + lr) * LDK + lk]));
+        for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-            bfr[j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(&Bs[(wn + 16 * j + lr) * LDK + lk]));
+            for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+                for (int r = 0; r < 4; ++r) {
+                    const int m = min(m0 + wm + 16 * i + 4 * (lane >> 4) + r, g.M - 1);
+                    const int n = min(n0 + wn + 16 * j + lr, g.N - 1);
+                    z[i][j][r] = g.z[(int64_t)m * g.ldz + n];
+                }
+    }
+    for (int k0 = kbeg; k0 < kend; k0 += GS * GK) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+        for (int s = 0; s < GS; ++s)
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                put<AT>(As + (s * T + t) * GT * LDK, fa[s][t]);
+                put<!BT>(Bs + (s * T + t) * GT * LDK, fb[s][t]);
+            }
+        __syncthreads();
+        if (k0 + GS * GK < kend) fetch(k0 + GS * GK);     // overlaps this step's products
+        const int left = (kend - k0 + GK - 1) / GK;
+#pragma unroll
+        for (int s = 0; s < GS; ++s) {
+            if (s >= left) break;
+            const uint16_t *ta = As + s * T * GT * LDK, *tb = Bs + s * T * GT * LDK;
+            bf16x8 af[NB], bfr[NB];
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+                af[i] =
+                    __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(&ta[(wm + 16 * i + lr) * LDK + lk]));
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                bfr[j] =
+                    __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(&tb[(wn + 16 * j + lr) * LDK + lk]));
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+        }
         __syncthreads();
     }
     float *cf = g.cf;
-    if (EPI == EPI_F32) cf += (int64_t)blockIdx.z * g.M * g.ldcf;
+    if (EPI == EPI_F32) cf += (int64_t)bz * g.M * g.ldcf;
     // lane holds C[4 (lane / 16) + r][lane % 16] of each 16 x 16 block
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int m = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
@@ -281,22 +343,76 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g)
                 } else if (EPI == EPI_F32) {
                     cf[(int64_t)m * g.ldcf + n] = v;
                 } else {
-                    g.cb[(int64_t)m * g.ldcb + n] = f2bf(v * gelu_grad_f(g.z[(int64_t)m * g.ldz + n]));
+                    g.cb[(int64_t)m * g.ldcb + n] = f2bf(v * gelu_grad_f(z[i][j][r]));
                 }
             }
 }
 
-// out[m][n] = sum over the splits z = 0 .. S-1, in that order, of
-// part[z][m][n] (pitch N).
-__global__ __launch_bounds__(256) void reduce_splits_kernel(int M, int N, int S, const float *part, float *out,
-                                                            int64_t ldo)
+// Workgroups go to the eight XCDs in turn, each with an L2 of its own.  The
+// grid is (kXcds, tiles / kXcds rounded up) and an XCD (blockIdx.x) takes
+// consecutive tiles, which share their operand rows.  Tiles past the end: none.
+// 16,384 rows forward 135 -> 115 us, 8,192 rows 80 -> 70.  The weight gradients
+// keep the launch order (a training step 178 us, 194 with consecutive tiles).
+constexpr int kXcds = 8;
+inline dim3 xcd_grid(int tiles) { return dim3(kXcds, (tiles + kXcds - 1) / kXcds); }
+__device__ inline int xcd_tile() { return (int)(blockIdx.x * gridDim.y + blockIdx.y); }
+
+template <bool AT, bool BT, int EPI>
+__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g, int gx, int tiles)
 {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ __attribute__((aligned(16))) uint16_t As[tile_lds<1>()];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[tile_lds<1>()];
+    const int t = xcd_tile();
+    if (t < tiles) gemm_tile<AT, BT, EPI, 1>(g, t % gx, t / gx, 0, 1, As, Bs);
+}
+
+// The weight gradients of several layers in one launch (one layer alone has
+// too few tiles to fill the chip, and each launch costs its gaps; with the
+// grouped reductions and bias sums a training step of 4,096 rows went from 315
+// to 208 us): workgroups first[l] .. first[l + 1] - 1 make layer l's tiles,
+// nz[l] K splits each.
+constexpr int kGroup = 8;
+struct DwGroup {
+    int n;
+    GemmArgs g[kGroup];           // cf: the gradient (nz = 1) or the splits' partial sums
+    int first[kGroup + 1], gx[kGroup], gy[kGroup], nz[kGroup];
+};
+
+template <int T>
+__global__ __launch_bounds__(256) void gemm_dw_kernel(DwGroup d)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t As[tile_lds<T>()];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[tile_lds<T>()];
+    const int tile = blockIdx.x;
+    int l = 0;
+    while (tile >= d.first[l + 1]) ++l;
+    const int r = tile - d.first[l], xy = d.gx[l] * d.gy[l], z = r / xy, t = r - z * xy;
+    gemm_tile<true, false, EPI_F32, T>(d.g[l], t % d.gx[l], t / d.gx[l], z, d.nz[l], As, Bs);
+}
+
+// out[m][n] = sum over the splits z = 0 .. S-1, in that order, of
+// part[z][m][n] (pitch N), for the layers of a group.
+struct ReduceGroup {
+    int n;
+    int M[kGroup], N[kGroup], S[kGroup], first[kGroup + 1];      // first: workgroups
+    const float *part[kGroup];
+    float *out[kGroup];
+    int64_t ldo[kGroup];
+};
+
+__global__ __launch_bounds__(256) void reduce_splits_kernel(ReduceGroup r)
+{
+    int l = 0;
+    while (l + 1 < r.n && (int)blockIdx.x >= r.first[l + 1]) ++l;
+    const int M = r.M[l], N = r.N[l], S = r.S[l];
+    const int64_t e = (int64_t)((int)blockIdx.x - r.first[l]) * 256 + threadIdx.x;
     if (e >= (int64_t)M * N) return;
     const int m = (int)(e / N), n = (int)(e - (int64_t)m * N);
+    const float *p = r.part[l] + e;
     float s = 0.0f;
-    for (int z = 0; z < S; ++z) s += part[(int64_t)z * M * N + e];
-    out[(int64_t)m * ldo + n] = s;
+#pragma unroll 4
+    for (int z = 0; z < S; ++z) s += p[(int64_t)z * M * N];
+    r.out[l][(int64_t)m * r.ldo[l] + n] = s;
 }
 
 // ------------------------------------------------ loss, grads, AdamW ----
@@ -326,38 +442,68 @@ __global__ __launch_bounds__(256) void mse_kernel(int n, int out_dim, int n_out,
     if (threadIdx.x == 0) part[blockIdx.x] = e2;
 }
 
-__global__ void loss_final_kernel(int nparts, const double *part, double scale, double *loss)
+// One wave: each lane adds every 64th partial sum, four reads in flight, then
+// the wave's sum.
+__global__ __launch_bounds__(64) void loss_final_kernel(int nparts, const double *part, double scale, double *loss)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
     double s = 0.0;
-    for (int i = 0; i < nparts; ++i) s += part[i];
-    *loss = s * scale;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nparts; i += 64) s += part[i];
+    s = wave_sum(s);
+    if (threadIdx.x == 0) *loss = s * scale;
 }
 
-// Column sums of a BF16 [M][N] matrix in two fixed-order passes: partial sums
-// over row slices (blockIdx.y, wave), then their sum.
+// Column sums of BF16 [M][N] matrices in two fixed-order passes: partial sums
+// over row slices (blockIdx.y, wave), then their sum; blockIdx.z: the matrix
+// (the bias gradients of several layers in one launch).  Eight rows' reads are
+// in flight together.
 constexpr int kColSlices = 16;
+struct ColGroup {
+    int M;
+    int N[kGroup];
+    const uint16_t *x[kGroup];
+    int64_t ldx[kGroup];
+    float *part[kGroup], *out[kGroup];
+};
 
-__global__ __launch_bounds__(256) void colsum_part_kernel(int M, int N, const uint16_t *x, int64_t ldx, float *part)
+__global__ __launch_bounds__(256) void colsum_part_kernel(ColGroup c)
 {
+    const int l = blockIdx.z, M = c.M, N = c.N[l];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = blockIdx.x * 64 + lane;
     const int nslice = kColSlices * NWAVE, slice = blockIdx.y * NWAVE + wave;
     const int per = (M + nslice - 1) / nslice;
     const int r0 = slice * per, r1 = min(M, r0 + per);
     if (n >= N) return;
+    const uint16_t *x = c.x[l] + n;
+    const int64_t ldx = c.ldx[l];
     float s = 0.0f;
-    for (int m = r0; m < r1; ++m) s += bf2f(x[(int64_t)m * ldx + n]);
-    part[(int64_t)slice * N + n] = s;
+    for (int m = r0; m < r1; m += 8) {
+        uint16_t v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = x[(int64_t)min(m + e, r1 - 1) * ldx];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (m + e < r1) s += bf2f(v[e]);
+    }
+    c.part[l][(int64_t)slice * N + n] = s;
 }
 
-__global__ void colsum_final_kernel(int N, const float *part, float *out)
+__global__ void colsum_final_kernel(ColGroup c)
 {
+    const int l = blockIdx.y, N = c.N[l];
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= N) return;
+    const float *part = c.part[l] + n;
     float s = 0.0f;
-    for (int i = 0; i < kColSlices * NWAVE; ++i) s += part[(int64_t)i * N + n];
-    out[n] = s;
+    for (int i = 0; i < kColSlices * NWAVE; i += 16) {
+        float v[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = part[(int64_t)(i + e) * N];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s += v[e];
+    }
+    c.out[l][n] = s;
 }
 
 // Decoupled weight decay Adam (Loshchilov and Hutter), then the BF16 copy.
@@ -660,8 +806,8 @@ template <bool AT, bool BT, int EPI>
 int gemm(const GemmArgs &g, hipStream_t st)
 {
     if (g.M <= 0 || g.N <= 0) return GM_OK;
-    dim3 grid((g.N + GT - 1) / GT, (g.M + GT - 1) / GT, 1);
-    hipLaunchKernelGGL((gemm_kernel<AT, BT, EPI>), grid, dim3(256), 0, st, g);
+    const int gx = (g.N + GT - 1) / GT, gy = (g.M + GT - 1) / GT;
+    hipLaunchKernelGGL((gemm_kernel<AT, BT, EPI>), xcd_grid(gx * gy), dim3(256), 0, st, g, gx, gx * gy);
     return launch_gemm_rc();
 }
 
@@ -683,27 +829,58 @@ size_t dw_part_floats(int M, int N, int K)
     return s > 1 ? (size_t)s * M * N : 0;
 }
 
-// C (FP32, pitch ldcf) = A^T B with A(m, k) = a[k * lda + m] and B(k, n) =
-// b[bmap(k) * ldb + n]: the weight gradients.  With more than one split the
-// splits write partial sums to `part` (dw_part_floats(M, N, K) floats) and a
-// second kernel adds them in split order, so the result does not depend on
-// timing.
-int gemm_dw(GemmArgs g, float *part, hipStream_t st)
+// C_l (FP32, pitch ldcf) = A_l^T B_l with A(m, k) = a[k * lda + m] and B(k, n) =
+// b[bmap(k) * ldb + n], l = 0 .. n - 1: the weight gradients.  With more than
+// one split the splits write partial sums to `part` (the layers' dw_part_floats
+// one after another) and a second kernel adds them in split order, so the
+// result does not depend on timing.
+int gemm_dw(const GemmArgs *g, int n, float *part, int num_cu, hipStream_t st)
 {
-    if (g.M <= 0 || g.N <= 0) return GM_OK;
-    const int s = dw_splits(g.M, g.N, g.K);
-    if (s == 1) return gemm<true, false, EPI_F32>(g, st);
-    float *out = g.cf;
-    const int64_t ldo = g.ldcf;
-    g.cf = part;
-    g.ldcf = g.N;
-    dim3 grid((g.N + GT - 1) / GT, (g.M + GT - 1) / GT, s);
-    hipLaunchKernelGGL((gemm_kernel<true, false, EPI_F32>), grid, dim3(256), 0, st, g);
-    if (hipGetLastError() != hipSuccess) return GM_EHIP;
-    const int64_t cnt = (int64_t)g.M * g.N;
-    hipLaunchKernelGGL(reduce_splits_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st, g.M, g.N, s,
-                       part, out, ldo);
-    return launch_gemm_rc();
+    for (int l0 = 0; l0 < n; l0 += kGroup) {
+        DwGroup d{};
+        ReduceGroup r{};
+        const int l1 = std::min(n, l0 + kGroup);
+        // 128 x 128 tiles read each operand half as often; taken where they still give two
+        // workgroups per CU (a training step of 4,096 rows 183 -> 172 us; of 512 rows 117 -> 122)
+        int64_t wide = 0;
+        for (int l = l0; l < l1; ++l)
+            wide += (int64_t)((g[l].M + 2 * GT - 1) / (2 * GT)) * ((g[l].N + 2 * GT - 1) / (2 * GT)) *
+                    dw_splits(g[l].M, g[l].N, g[l].K);
+        const int T = wide >= 2 * (int64_t)num_cu ? 2 : 1;
+        int wgs = 0, rwgs = 0;
+        for (int l = l0; l < l1; ++l) {
+            if (g[l].M <= 0 || g[l].N <= 0) continue;
+            const int k = d.n++, s = dw_splits(g[l].M, g[l].N, g[l].K);
+            d.g[k] = g[l];
+            d.gx[k] = (g[l].N + GT * T - 1) / (GT * T);
+            d.gy[k] = (g[l].M + GT * T - 1) / (GT * T);
+            d.nz[k] = s;
+            d.first[k] = wgs;
+            wgs += d.gx[k] * d.gy[k] * s;
+            d.first[k + 1] = wgs;
+            if (s > 1) {
+                const int64_t cnt = (int64_t)g[l].M * g[l].N;
+                const int q = r.n++;
+                r.M[q] = g[l].M;
+                r.N[q] = g[l].N;
+                r.S[q] = s;
+                r.part[q] = part;
+                r.out[q] = g[l].cf;
+                r.ldo[q] = g[l].ldcf;
+                r.first[q] = rwgs;
+                rwgs += (int)((cnt + 255) / 256);
+                d.g[k].cf = part;
+                d.g[k].ldcf = g[l].N;
+                part += (size_t)s * cnt;
+            }
+        }
+        if (wgs && T == 2) hipLaunchKernelGGL(gemm_dw_kernel<2>, dim3(wgs), dim3(256), 0, st, d);
+        if (wgs && T == 1) hipLaunchKernelGGL(gemm_dw_kernel<1>, dim3(wgs), dim3(256), 0, st, d);
+        if (hipGetLastError() != hipSuccess) return GM_EHIP;
+        if (rwgs) hipLaunchKernelGGL(reduce_splits_kernel, dim3(rwgs), dim3(256), 0, st, r);
+        if (hipGetLastError() != hipSuccess) return GM_EHIP;
+    }
+    return GM_OK;
 }
 
 // Forward pass of n rows of x (BF16, row pitch ldx, optional row gather).
@@ -753,11 +930,11 @@ size_t train_ws_bytes(const gm_mlp *m, int n)
     }
     add((size_t)n * m->out_dim * 4);        // out
     add((size_t)n * m->out_dim * 2);        // dO
-    add((size_t)n * m->hidden * 2 * 2);     // dZ ping-pong
-    add((size_t)kColSlices * NWAVE * std::max(m->hidden, m->out_dim) * 4);
+    add((size_t)n * m->hidden * 2);         // dZ of the last hidden layer
+    for (int l = 0; l < L; ++l) add((size_t)kColSlices * NWAVE * layer_out(m, l) * 4);
     add((size_t)((n + 15) / 16) * 8);       // loss partials
     size_t part = 0;                        // K-split partial sums of the weight gradients
-    for (int l = 0; l < L; ++l) part = std::max(part, dw_part_floats(layer_out(m, l), layer_in(m, l), n));
+    for (int l = 0; l < L; ++l) part += dw_part_floats(layer_out(m, l), layer_in(m, l), n);
     add(part * 4);
     return b + 256;
 }
@@ -777,13 +954,16 @@ int backward_pass(gm_ctx *c, const gm_mlp *m, int n, const uint16_t *x, int64_t 
     }
     float *out = cv.take<float>((size_t)n * m->out_dim);
     uint16_t *dout = cv.take<uint16_t>((size_t)n * m->out_dim);
-    uint16_t *dz[2] = {cv.take<uint16_t>((size_t)2 * n * m->hidden), nullptr};
-    dz[1] = dz[0] + (size_t)n * m->hidden;
-    float *cpart = cv.take<float>((size_t)kColSlices * NWAVE * std::max(m->hidden, m->out_dim));
+    uint16_t *dz[17];       // dZ_l takes the place of Z_{l+1}, whose last reader is dZ_{l+1}
+    for (int l = 0; l < L - 2; ++l) dz[l] = reinterpret_cast<uint16_t *>(Z[l + 1]);
+    dz[L - 2] = cv.take<uint16_t>((size_t)n * m->hidden);
+    dz[L - 1] = dout;
+    float *cpart[17];
+    for (int l = 0; l < L; ++l) cpart[l] = cv.take<float>((size_t)kColSlices * NWAVE * layer_out(m, l));
     const int nblk = (n + 15) / 16;
     double *lpart = cv.take<double>((size_t)nblk);
     size_t npart = 0;
-    for (int l = 0; l < L; ++l) npart = std::max(npart, dw_part_floats(layer_out(m, l), layer_in(m, l), n));
+    for (int l = 0; l < L; ++l) npart += dw_part_floats(layer_out(m, l), layer_in(m, l), n);
     float *dwpart = cv.take<float>(npart);
     rc = forward_pass(m, n, x, ldx, rows, Y, Z, out, st);
     if (rc) return rc;
@@ -795,49 +975,54 @@ int backward_pass(gm_ctx *c, const gm_mlp *m, int n, const uint16_t *x, int64_t 
                            1.0 / ((double)n * m->n_out), loss_out);
         if (hipGetLastError() != hipSuccess) return GM_EHIP;
     }
-    const uint16_t *dcur = dout;
-    int64_t ldd = m->out_dim;
-    for (int l = L - 1; l >= 0; --l) {
-        const int nin = layer_in(m, l), nout = layer_out(m, l);
-        // dW_l[o][i] = sum_m dZ_l[m][o] X_l[m][i]
-        GemmArgs g{};
-        g.M = nout;
-        g.N = nin;
-        g.K = n;
-        g.a = dcur;
-        g.lda = ldd;
-        g.b = l == 0 ? x : Y[l - 1];
-        g.ldb = l == 0 ? ldx : m->hidden;
-        g.bmap = l == 0 ? rows : nullptr;
-        g.cf = m->grad + w_off(m, l);
-        g.ldcf = nin;
-        rc = gemm_dw(g, dwpart, st);
-        if (rc) return rc;
-        hipLaunchKernelGGL(colsum_part_kernel, dim3((nout + 63) / 64, kColSlices), dim3(256), 0, st, n, nout, dcur,
-                           ldd, cpart);
-        hipLaunchKernelGGL(colsum_final_kernel, dim3((nout + 255) / 256), dim3(256), 0, st, nout, cpart,
-                           m->grad + b_off(m, l));
-        if (hipGetLastError() != hipSuccess) return GM_EHIP;
-        if (l > 0) {
-            // dZ_{l-1} = (dZ_l W_l) * gelu'(Z_{l-1})
-            GemmArgs d{};
-            d.M = n;
-            d.N = nin;
-            d.K = nout;
-            d.a = dcur;
-            d.lda = ldd;
-            d.b = m->params_bf16 + w_off(m, l);
-            d.ldb = nin;
-            uint16_t *dnext = dz[l & 1];
-            d.cb = dnext;
-            d.ldcb = m->hidden;
-            d.z = Z[l - 1];
-            d.ldz = m->hidden;
-            rc = gemm<false, false, EPI_DGELU>(d, st);
-            if (rc) return rc;
-            dcur = dnext;
-            ldd = m->hidden;
+    // dZ_{l-1} = (dZ_l W_l) * gelu'(Z_{l-1}), down the network
+    for (int l = L - 1; l > 0; --l) {
+        GemmArgs d{};
+        d.M = n;
+        d.N = layer_in(m, l);
+        d.K = layer_out(m, l);
+        d.a = dz[l];
+        d.lda = layer_out(m, l);
+        d.b = m->params_bf16 + w_off(m, l);
+        d.ldb = layer_in(m, l);
+        d.cb = dz[l - 1];
+        d.ldcb = m->hidden;
+        d.z = Z[l - 1];
+        d.ldz = m->hidden;
+        if ((rc = gemm<false, false, EPI_DGELU>(d, st))) return rc;
+    }
+    // dW_l[o][i] = sum_m dZ_l[m][o] X_l[m][i] and db_l[o] = sum_m dZ_l[m][o], every layer together
+    GemmArgs g[17]{};
+    for (int l = 0; l < L; ++l) {
+        g[l].M = layer_out(m, l);
+        g[l].N = layer_in(m, l);
+        g[l].K = n;
+        g[l].a = dz[l];
+        g[l].lda = layer_out(m, l);
+        g[l].b = l == 0 ? x : Y[l - 1];
+        g[l].ldb = l == 0 ? ldx : m->hidden;
+        g[l].bmap = l == 0 ? rows : nullptr;
+        g[l].cf = m->grad + w_off(m, l);
+        g[l].ldcf = layer_in(m, l);
+    }
+    if ((rc = gemm_dw(g, L, dwpart, c->num_cu, st))) return rc;
+    for (int l0 = 0; l0 < L; l0 += kGroup) {
+        ColGroup c{};
+        c.M = n;
+        const int k = std::min(kGroup, L - l0);
+        int most = 0;
+        for (int i = 0; i < k; ++i) {
+            const int l = l0 + i;
+            c.N[i] = layer_out(m, l);
+            c.x[i] = dz[l];
+            c.ldx[i] = layer_out(m, l);
+            c.part[i] = cpart[l];
+            c.out[i] = m->grad + b_off(m, l);
+            most = std::max(most, c.N[i]);
         }
+        hipLaunchKernelGGL(colsum_part_kernel, dim3((most + 63) / 64, kColSlices, k), dim3(256), 0, st, c);
+        hipLaunchKernelGGL(colsum_final_kernel, dim3((most + 63) / 64, k), dim3(64), 0, st, c);
+        if (hipGetLastError() != hipSuccess) return GM_EHIP;
     }
     return GM_OK;
 }
@@ -1053,7 +1238,7 @@ int gm_mlp_gemm(gm_ctx *ctx, int32_t op, int32_t m, int32_t n, int32_t k, const 
     const size_t part = dw_part_floats(m, n, k);
     int rc = ensure_ws(ctx, part * 4 + 256);
     if (rc) return rc;
-    return gemm_dw(g, reinterpret_cast<float *>(ctx->mlp_ws), st);
+    return gemm_dw(&g, 1, reinterpret_cast<float *>(ctx->mlp_ws), ctx->num_cu, st);
 }
 
 int gm_mlp_backward(gm_ctx *ctx, const gm_mlp *mlp, int32_t n, const uint16_t *x, int64_t ldx, const int32_t *rows,
