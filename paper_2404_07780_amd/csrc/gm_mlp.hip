@@ -531,8 +531,8 @@ __global__ void sync_bf16_kernel(int64_t count, const float *p, uint16_t *pb)
 
 // ------------------------------------------------------- features -------
 // mom8[g] = {sky0, F0, xc, yc, m_g, r0, q0, theta0}, pk[g] = the peak (both nullable)
-// 16,384 cutouts of 64 x 64: 790 -> 355 us (floor: 570 MB, 110 us).  Bound by
-// instruction issue (moments 265 us, cells and the last wave's functions 90);
+// 16,384 cutouts of 64 x 64: 790 -> 360 us (floor: 570 MB, 110 us).  Bound by
+// instruction issue (moments 270 us, cells and the last wave's functions 90);
 // before, by three passes over memory and a fourth for the cells.  Four
 // workgroups per CU (118 VGPRs): with 256 VGPRs 530 us, with five or six
 // workgroups the pixels spill (520, 750).
