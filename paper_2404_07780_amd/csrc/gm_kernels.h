@@ -553,7 +553,8 @@ __device__ inline void load_taps(const float *psl, int u, float (&tp)[KP])
 // 4 b + t: x = b, output t; 0 outside the PSF).  It is a fused multiply-add
 // with one rounding (also for denormals), and x runs downwards, so each
 // accumulator sees the products of the scalar loop in its order: the results
-// are the same bits (the extra products are 0 x finite).  One instruction of 8
+// are the same bits (the extra products are 0 x finite; conv_group sees to
+// strips with infinite elements).  One instruction of 8
 // cycles replaces four FMAs, which a single wave per SIMD issues at best every
 // 5 cycles (two waves together: every 2.6); matrix and vector instructions of
 // two waves do not overlap (both measured), so what bounds the convolutions is
@@ -1002,10 +1003,33 @@ __device__ inline void conv64(const float *buf, int K, const cfloat *psf, const 
     else conv64_any(b64, r, K, region_wp(K), psl, acc0);
 }
 
+// One FP32 plane by scalar products, each output's own taps alone: for strips
+// in which the matrix cores met an infinite element (p as conv_one's).
+__device__ inline void conv_strip(const float *p, int K, int IWP, const float *psl, float (&out)[4])
+{
+    const int kp = psf_pitch(K);
+    float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (int u = 0; u < K; ++u)
+#pragma unroll 1
+        for (int v = 0; v < K; ++v) {
+            const float pv = psl[u * kp + v];
+            const float *s = p - u * IWP + K - 1 - v;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) a[t] = fmaf(pv, s[t], a[t]);
+        }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) out[t] = a[t];
+}
+
 // Convolve planes LO..HI-1 for this thread's 1 x 4 output strip (tile row r,
 // columns 4 cg .. 4 cg + 3): plane 0 in FP64 on the vector units, the FP32
 // planes two at a time on the matrix cores.  KT > 0: compile-time PSF side;
-// 0: any K.
+// 0: any K.  A matrix instruction multiplies an element by zero for the
+// outputs of the strip whose PSF does not reach it; an infinite element (a
+// derivative beyond FP32's range) makes those NaN, so a strip that holds a NaN
+// is convolved anew by scalar products (v_maximum3_f32, which keeps a NaN,
+// looks at two values an instruction).
 template <class F, int KT, int LO, int HI>
 __device__ inline void conv_group(const float *__restrict__ buf, int K, const cfloat *psf, const float *psl, int r,
                                   int cg, double (&acc0)[4], float (&acc)[F::NPL][4])
@@ -1052,6 +1076,29 @@ __device__ inline void conv_group(const float *__restrict__ buf, int K, const cf
         else conv_any<false>(p, K, IWP, psl, none, one);
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[HI - 1][t] = one[t];
+    }
+    if constexpr (NP > 0) {
+        float all = 0.0f;
+#pragma unroll
+        for (int q = QLO; q < HI; ++q)
+#pragma unroll
+            for (int t = 0; t < 4; t += 2)
+                all = __builtin_elementwise_maximum(__builtin_elementwise_maximum(all, acc[q][t]), acc[q][t + 1]);
+        if (__builtin_expect(all != all, 0)) {
+            int tid = threadIdx.x, row, col;       // worked out anew: nothing is kept for this path
+            asm volatile("" : "+v"(tid));
+            strip_of(tid, K, row, col);
+            const float *p = buf + (LO == 0 ? 2 * plane_sz : 0) + 4 * col + (row + K - 1) * IWP;
+#pragma unroll 1
+            for (int pl = 0; pl < NP; ++pl) {
+                float o[4];
+                conv_strip(p + pl * plane_sz, K, IWP, psl, o);
+#pragma unroll
+                for (int q = QLO; q < HI; ++q)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) acc[q][t] = q - QLO == pl ? o[t] : acc[q][t];
+            }
+        }
     }
 }
 
