@@ -166,6 +166,7 @@ struct EvalShared {
     double win0[F::NCOMP][MAXWIN];
     float win[F::NCOMP][MAXWIN][F::ND];
     double c2[NWAVE];                                     // per-wave chi^2
+    int exact, pad;                                       // 1: strips with a NaN anew (conv_group)
     double nacc[NWAVE][F::P + F::P * (F::P + 1) / 2];     // per-wave FP64 sums of the flushed partials
 };
 
@@ -1015,14 +1016,21 @@ __device__ inline void conv_strip(const float *p, int K, int IWP, const float *p
     const int kp = psf_pitch(K);
     float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll 1
-    for (int u = 0; u < K; ++u)
-#pragma unroll 1
+    for (int u = 0; u < K; ++u) {
+        const float *rp = p - u * IWP, *pr = psl + u * kp;
+        float s1 = rp[K], s2 = rp[K + 1], s3 = rp[K + 2];
+#pragma unroll 4
         for (int v = 0; v < K; ++v) {
-            const float pv = psl[u * kp + v];
-            const float *s = p - u * IWP + K - 1 - v;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) a[t] = fmaf(pv, s[t], a[t]);
+            const float s0 = rp[K - 1 - v], pv = pr[v];
+            a[0] = fmaf(pv, s0, a[0]);
+            a[1] = fmaf(pv, s1, a[1]);
+            a[2] = fmaf(pv, s2, a[2]);
+            a[3] = fmaf(pv, s3, a[3]);
+            s3 = s2;
+            s2 = s1;
+            s1 = s0;
         }
+    }
 #pragma unroll
     for (int t = 0; t < 4; ++t) out[t] = a[t];
 }
@@ -1033,11 +1041,11 @@ __device__ inline void conv_strip(const float *p, int K, int IWP, const float *p
 // 0: any K.  A matrix instruction multiplies an element by zero for the
 // outputs of the strip whose PSF does not reach it; an infinite element (a
 // derivative beyond FP32's range) makes those NaN, so a strip that holds a NaN
-// is convolved anew by scalar products (v_maximum3_f32, which keeps a NaN,
-// looks at two values an instruction).
+// is convolved anew by scalar products where *exact is set (v_maximum3_f32,
+// which keeps a NaN, looks at two values an instruction).
 template <class F, int KT, int LO, int HI>
 __device__ inline void conv_group(const float *__restrict__ buf, int K, const cfloat *psf, const float *psl, int r,
-                                  int cg, double (&acc0)[4], float (&acc)[F::NPL][4])
+                                  int cg, double (&acc0)[4], float (&acc)[F::NPL][4], const int *exact)
 {
     const int IH = region_h(K), IWP = region_wp(K);
     const int plane_sz = IH * IWP;
@@ -1083,6 +1091,7 @@ __device__ inline void conv_group(const float *__restrict__ buf, int K, const cf
         for (int t = 0; t < 4; ++t) acc[HI - 1][t] = one[t];
     }
     if constexpr (NP > 0) {
+        if (uniform(*exact) == 0) return;
         float all = 0.0f;
 #pragma unroll
         for (int q = QLO; q < HI; ++q)
@@ -1094,8 +1103,15 @@ __device__ inline void conv_group(const float *__restrict__ buf, int K, const cf
             asm volatile("" : "+v"(tid));
             strip_of(tid, K, row, col);
             const float *p = buf + (LO == 0 ? 2 * plane_sz : 0) + 4 * col + (row + K - 1) * IWP;
+            unsigned which = 0;
+#pragma unroll
+            for (int q = QLO; q < HI; ++q) {
+                const float x = (acc[q][0] + acc[q][1]) + (acc[q][2] + acc[q][3]);
+                which |= (x != x ? 1u : 0u) << (q - QLO);
+            }
 #pragma unroll 1
             for (int pl = 0; pl < NP; ++pl) {
+                if (!((which >> pl) & 1u)) continue;
                 float o[4];
                 conv_strip(p + pl * plane_sz, K, IWP, psl, o);
 #pragma unroll
@@ -1117,7 +1133,7 @@ __device__ inline void tile_planes(const EvalShared<F> &sh, float *buf, int H, i
         constexpr int LO = group_bound(F::NPL, NG, G), HI = group_bound(F::NPL, NG, G + 1);
         fill_region<F, LO, HI, shift64<KT>()>(sh, buf, H, W, K, ti0, tj0);
         __syncthreads();
-        conv_group<F, KT, LO, HI>(buf, K, psf, psl, r, cg, acc0, acc);
+        conv_group<F, KT, LO, HI>(buf, K, psf, psl, r, cg, acc0, acc, &sh.exact);
         __syncthreads();
         tile_planes<F, KT, NG, G + 1>(sh, buf, H, W, K, ti0, tj0, psf, psl, r, cg, acc0, acc);
     }
@@ -2271,6 +2287,20 @@ __device__ void lm_step(LMShared<F> &s, const FitArgs &fa, int H, int W)
     }
 }
 
+// The evaluation just made will be taken (as in lm_step), it was not exact,
+// and a derivative was NaN at a pixel in use, which the diagonal of its A
+// shows.  Most trials with infinite derivatives, which throw a magnitude far
+// out, are rejected by their chi^2 (512 bulge + disk fits of 128 x 128 took
+// 63 ms instead of 56 with the exact convolution at once).
+template <class F>
+__device__ inline bool lm_spoilt(const LMShared<F> &s, int exact)
+{
+    const int k = min((int)(threadIdx.x & 63), F::P - 1);
+    const double d = s.At[k * F::P + k];
+    const bool take = isfinite(s.chi2t) && (s.t < 0 || s.chi2t < s.chi2);
+    return !exact && take && __ballot(d != d) != 0;
+}
+
 template <class F>
 __device__ void load_u(LMShared<F> &s, const ModelArgs &ma, const double *params)
 {
@@ -2399,6 +2429,7 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
             __syncthreads();      // s.gal is rewritten by thread 0 next
             continue;
         }
+        if (tid == 0) esh.exact = tsize > 1;
         int src = fa.n_boot > 0 ? g / fa.n_boot : g;
         const BootArgs bt{fa.boot_k0, fa.boot_k1, src, fa.n_boot > 0 ? g - src * fa.n_boot : -1};
         Meta me = ba.meta[src];
@@ -2485,11 +2516,16 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
                         continue;
                     }
                     ++epoch;
+                } else if (lm_spoilt<F>(s, esh.exact)) {
+                    __syncthreads();
+                    if (tid == 0) esh.exact = 1;      // once more
+                    continue;
                 }
             }
             if (!member) {
                 if (uniform(tid >> 6) < 2) lm_step<F>(s, fa, me.h, me.w);
                 else __syncthreads();         // lm_step's barrier
+                if (tid == 0) esh.exact = tsize > 1;
             }
             __syncthreads();
         }
@@ -2545,7 +2581,10 @@ __global__ __launch_bounds__(NT) void errors_kernel(ModelArgs ma, BatchArgs ba, 
     const int tid = threadIdx.x;
     for (int g = blockIdx.x; g < ea.n_gal; g += gridDim.x) {
         const Meta me = ba.meta[g];
-        if (tid == 0) load_u<F>(s, ma, ea.params + (int64_t)g * ma.p);
+        if (tid == 0) {
+            load_u<F>(s, ma, ea.params + (int64_t)g * ma.p);
+            esh.exact = 1;
+        }
         __syncthreads();
         evaluate<F, KT, NG>(s.u, ma, ba, me, esh, planes, &s.chi2, s.g, s.A);
         if (tid == 0) {
@@ -2620,6 +2659,7 @@ __global__ __launch_bounds__(NT, 2) void image_kernel(ModelArgs ma, BatchArgs ba
         const Meta me = ba.meta[g];
         const int H = me.h, W = me.w, K = KT > 0 ? KT : me.k;
         if (tid == 0) {
+            esh.exact = 1;
             const double *pp = ia.params + (int64_t)g * ma.p;
             for (int k = 0; k < P; ++k) {
                 int c = ma.col[k];
