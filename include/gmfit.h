@@ -163,7 +163,8 @@ int gm_jacobian(gm_ctx *ctx, const gm_model *model, const gm_batch *batch,
  *   team_wait_us -- bound of every wait between the workgroups of a team, in
  *     microseconds (0 = 20 s); a fit whose team passes it ends with
  *     GM_ST_TEAM_TIMEOUT (the waits always end: a team's workgroups are
- *     resident together). */
+ *     resident together).  A fit that waits longer for a helper's tile makes
+ *     that tile and the rest of its evaluations itself, with the same result. */
 typedef struct {
     int32_t plane_groups;
     int32_t wg_per_cu;
@@ -177,6 +178,13 @@ typedef struct {
  * if the family has no compiled variant with that many plane groups; a
  * variant whose LDS does not fit a batch's PSF side falls back to the default. */
 int gm_set_schedule(gm_ctx *ctx, const gm_model *model, int32_t psf_k, const gm_schedule *sched);
+
+/* What the helpers (see team) of the context's last fitting launch with
+ * helpers did: counts_out[5] (host) = {helpers at its end, workgroups that
+ * turned helpers, helpers that left before the last fit's end, tiles made by
+ * helpers, evaluations whose wait for a helper's tile passed team_wait_us};
+ * zeros before the first such launch.  Waits for the device. */
+int gm_help_counts(gm_ctx *ctx, int32_t *counts_out);
 
 /* The plane-group counts compiled for the family of `model` that fit LDS at
  * PSF side psf_k (odd), preferred first: up to cap into plane_groups_out, the

@@ -823,6 +823,19 @@ int gm_set_schedule(gm_ctx *ctx, const gm_model *model, int32_t psf_k, const gm_
     return GM_OK;
 }
 
+int gm_help_counts(gm_ctx *ctx, int32_t *counts_out)
+{
+    if (!ctx || !counts_out) return GM_EINVAL;
+    int32_t head[6] = {0, 0, 0, 0, 0, 0};        // the first words of the helpers' board
+    if (ctx->help) {
+        if (hipDeviceSynchronize() != hipSuccess) return GM_EHIP;
+        if (hipMemcpy(head, ctx->help, sizeof(head), hipMemcpyDeviceToHost) != hipSuccess) return GM_EHIP;
+    }
+    const int at[5] = {0, 2, 3, 4, 5};
+    for (int i = 0; i < 5; ++i) counts_out[i] = head[at[i]];
+    return GM_OK;
+}
+
 int gm_schedule_options(const gm_model *model, int32_t psf_k, int32_t *plane_groups_out, int32_t cap,
                         int32_t *n_out)
 {

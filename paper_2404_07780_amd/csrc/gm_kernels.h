@@ -1228,8 +1228,9 @@ __device__ inline void boot_weights(const BootArgs &bt, int64_t pix0, float (&m)
 // frees entries by advancing `added`.  The tile the owner waits for is held by
 // a running workgroup, whose entry is free, so every wait ends; each is bounded
 // by spin_limit all the same: past it the owner makes the tile itself and
-// leaves the slot for good (a late helper can then only write to that slot),
-// and a helper that finds nothing to do for that long ends.
+// leaves the slot for good (a late helper can then only write to that slot).
+// A helper leaves, and is no longer counted, when no fit ended and it found no
+// tile for idle_limit.
 // The board is zeroed before every launch; slots past n_slots are never used.
 constexpr int kHelpSlots = 64;
 constexpr int kHelpRing = 16;
@@ -1242,10 +1243,12 @@ struct HelpSlot {
     int seq[kHelpRing];
     int pad[12];
 };
-struct HelpBoard {
-    int idle;                     // workgroups that have turned helpers
+struct HelpBoard {                // the first six words: gm_help_counts
+    int idle;                     // helpers
     int done;                     // queue entries finished
-    int pad[14];
+    int turned, left;             // workgroups that turned helpers; that left before the last fit's end
+    int tiles, lost;              // tiles made by helpers; evaluations that went on without one
+    int pad[10];
     unsigned long long ticket[kHelpSlots];      // epoch << 32 | tiles << 16 | next
     HelpSlot slot[kHelpSlots];
 };
@@ -1283,6 +1286,10 @@ __device__ inline void agent_store(T *p, T v)
 // invalidation would hit every workgroup of the die (with them, 2,048 fits of
 // 64 x 64 ran 12% slower helped than alone).
 __device__ inline void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ inline int help_count(int *p, int n)
+{
+    return __hip_atomic_fetch_add(p, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ inline int help_seq(int epoch, int tile) { return (epoch << 11) | (tile + 1); }
 __device__ inline unsigned long long help_take(unsigned long long *ticket)
 {
@@ -1416,6 +1423,7 @@ __device__ inline int help_next(HelpState &hp, int next, int ntiles, int &held, 
         if (wall_clock64() - t0 > hp.limit) {
             lost = 1;
             agent_store(hp.board->ticket + hp.slot, 0ull);
+            help_count(&hp.board->lost, 1);
             return TILE_SUM;
         }
         __builtin_amdgcn_s_sleep(2);
@@ -1424,8 +1432,8 @@ __device__ inline int help_next(HelpState &hp, int next, int ntiles, int &held, 
 }
 
 // Helper, wave 0: takes a tile of some open evaluation into hp; false when
-// every fit has ended, or nothing was found for the limit's time.
-__device__ inline bool help_find(HelpState &hp, int n_entries)
+// every fit has ended, or when no fit ended and no tile was found for idle_limit.
+__device__ inline bool help_find(HelpState &hp, int n_entries, int64_t idle_limit)
 {
     static_assert(kHelpSlots == 64, "one lane per slot");
     HelpBoard *bd = hp.board;
@@ -1440,7 +1448,11 @@ __device__ inline bool help_find(HelpState &hp, int n_entries)
         if (done != seen) {
             seen = done;
             t0 = now;
-        } else if (now - t0 > hp.limit) {
+        } else if (now - t0 > idle_limit) {
+            if (lane == 0) {
+                help_count(&bd->idle, -1);
+                help_count(&bd->left, 1);
+            }
             return false;
         }
         // lane l looks at slot (l + turn) mod 64, so that helpers spread
@@ -1560,7 +1572,10 @@ __device__ __forceinline__ void evaluate(const double *u, const ModelArgs &ma, c
             }
             help_strip<F, true>(hp->buf(), ti, acc0, acc);
             help_publish(hs->seq + ti % kHelpRing, help_seq(hp->epoch, ti));
-            if (role == HELP_HELPER) return;
+            if (role == HELP_HELPER) {
+                if (tid == 0) ++sh_help[3];
+                return;
+            }
             continue;
         }
         if (mode == TILE_LOAD) help_strip<F, false>(hp->buf(), ti, acc0, acc);
@@ -1863,7 +1878,8 @@ struct LMShared {
     int damped;               // the damped step: 1 factorised, 2 below the tolerance
     int gal;
     int tok;                  // team: the last wait ended in time
-    int help[3];              // helpers: idle count, then tile / mode / lost of the next step
+    int help[4];              // owner: a helper to be had, then tile / mode / lost of the next step;
+                              // helper: slot / epoch / tile taken / tiles made
 };
 
 struct FitArgs {
@@ -1904,6 +1920,7 @@ struct FitArgs {
     struct HelpBoard *help;
     char *help_buf;
     int64_t help_stride;      // bytes of help_buf per slot
+    int64_t idle_limit;       // helpers' wait for work
     int help_slots;
     int grid_items;           // workgroups worth launching (at least the queue entries)
 };
@@ -2302,7 +2319,7 @@ __device__ inline bool lm_spoilt(const LMShared<F> &s, int exact)
 }
 
 template <class F>
-__device__ void load_u(LMShared<F> &s, const ModelArgs &ma, const double *params)
+__device__ __forceinline__ void load_u(LMShared<F> &s, const ModelArgs &ma, const double *params)
 {
     for (int k = 0; k < F::P; ++k) {
         int c = ma.col[k];
@@ -2413,7 +2430,11 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
         int g = 0, trank = 0, tsize = 1, team = 0;
         if (helper) {
             hp.role = HELP_HELPER;
-            if (tid == 0) __hip_atomic_fetch_add(&fa.help->idle, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0) {
+                help_count(&fa.help->idle, 1);
+                help_count(&fa.help->turned, 1);
+                s.help[3] = 0;
+            }
         } else if (fa.items) {
             const TeamItem it = fa.items[qi];
             g = uniform(it.fit);
@@ -2424,8 +2445,7 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
             g = uniform(fa.order[qi]);
         }
         if (!helper && fa.active && uniform(fa.active[g]) == 0) {
-            if (fa.help && tid == 0)
-                __hip_atomic_fetch_add(&fa.help->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (fa.help && tid == 0) help_count(&fa.help->done, 1);
             __syncthreads();      // s.gal is rewritten by thread 0 next
             continue;
         }
@@ -2444,7 +2464,7 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
         for (;;) {
             if (helper) {
                 if (tid < 64) {
-                    const bool any = help_find(hp, fa.n_gal);
+                    const bool any = help_find(hp, fa.n_gal, fa.idle_limit);
                     if (tid == 0) {
                         s.action = any ? ACT_EVAL : ACT_DONE;
                         s.help[0] = hp.slot;
@@ -2529,7 +2549,10 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
             }
             __syncthreads();
         }
-        if (helper) break;
+        if (helper) {
+            if (tid == 0) help_count(&fa.help->tiles, s.help[3]);
+            break;
+        }
         if (member) {
             __syncthreads();          // s.gal is rewritten by thread 0 next
             continue;
@@ -2537,7 +2560,7 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
         if (tid == 0 && fa.help) {
             if (hp.slot >= 0)
                 agent_store(&fa.help->slot[hp.slot].owner, 0);
-            __hip_atomic_fetch_add(&fa.help->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            help_count(&fa.help->done, 1);
         }
         if (tsize > 1 && tid == 0) {
             // end the team (epoch + 2 exceeds every epoch a member can be waiting for)

@@ -373,6 +373,7 @@ int run_fit(gm_ctx *c, const CallInfo &ci, const gm_fit_opts *o, double *params,
     fa.part = team_part;
     fa.part_stride = part_stride;
     const int64_t hz = std::max<int64_t>(c->wall_hz, 1000000);
+    fa.idle_limit = 20 * hz;
     fa.spin_limit = ci.team_wait_us > 0 ? std::max<int64_t>(1, hz * ci.team_wait_us / 1000000) : 20 * hz;
     fa.active = o ? o->active : nullptr;
     fa.n_gal = n_items;

@@ -25,7 +25,7 @@ SERSIC, EXPDISK, FERRER, KING, GAUSSIAN, MOFFAT, SKY, SKYPLANE = range(1, 9)
 # exported symbols (one per declaration of include/gmfit.h)
 SYMBOLS = ("gm_create", "gm_destroy", "gm_error_string", "gm_model_image", "gm_jacobian",
            "gm_default_guess", "gm_fit_batch", "gm_fit_batch_noalloc", "gm_param_errors", "gm_model_vjp", "gm_set_schedule",
-           "gm_schedule_options", "gm_mlp_param_count", "gm_mlp_sync",
+           "gm_schedule_options", "gm_help_counts", "gm_mlp_param_count", "gm_mlp_sync",
            "gm_mlp_forward", "gm_mlp_backward", "gm_mlp_adamw", "gm_mlp_train_step", "gm_mlp_gemm", "gm_features",
            "gm_proposal_targets", "gm_proposal_decode", "gm_fit_learned", "gm_synth_noise",
            "gm_plan_fit", "gm_plan_fit_learned", "gm_plan_launch", "gm_plan_elapsed", "gm_plan_destroy",
@@ -106,6 +106,8 @@ def lib() -> C.CDLL:
         L.gm_model_vjp.argtypes = [v, p, p, v, v, v, v]
         L.gm_set_schedule.argtypes = [v, p, i, p]
         L.gm_schedule_options.argtypes = [p, i, v, i, v]
+        L.gm_help_counts.argtypes = [v, v]
+        L.gm_help_counts.restype = i
         i64, u64, f, d = C.c_int64, C.c_uint64, C.c_float, C.c_double
         L.gm_mlp_param_count.argtypes = [p]
         L.gm_mlp_param_count.restype = i64
@@ -316,7 +318,8 @@ def gm_set_schedule(model: Model, psf_k: int, plane_groups: int = 0, wg_per_cu: 
     """Schedule of the model's family at PSF side psf_k (0: every side without
     one): plane groups, persistent workgroups per CU, workgroups per fit
     (team: 0 automatic, 1 one, k > 1 up to k for fits of at least
-    team_min_tiles tiles) and the bound of a team's waits (0: 20 s)."""
+    team_min_tiles tiles) and the bound of a team's waits and of those for
+    helpers' tiles (0: 20 s)."""
     ctx = ctx or context()
     m = model.c()
     sc = gm_schedule(int(plane_groups), int(wg_per_cu), int(team), int(team_min_tiles), int(team_wait_us))
@@ -331,6 +334,15 @@ def gm_schedule_options(model: Model, psf_k: int) -> List[int]:
     n = C.c_int32()
     _check("gm_schedule_options", lib().gm_schedule_options(C.byref(m), int(psf_k), buf, 8, C.byref(n)))
     return [int(buf[i]) for i in range(min(n.value, 8))]
+
+
+def gm_help_counts(ctx: Optional[Context] = None) -> dict:
+    """What the helpers of the context's last fitting launch with helpers did
+    (gmfit.h); waits for the device."""
+    ctx = ctx or context()
+    buf = (C.c_int32 * 5)()
+    _check("gm_help_counts", lib().gm_help_counts(ctx.handle, buf))
+    return dict(zip(("idle", "turned", "left", "tiles", "lost"), map(int, buf)))
 
 
 def gm_model_vjp(model: Model, batch: Batch, params, grad_image: torch.Tensor,
