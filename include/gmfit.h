@@ -158,7 +158,10 @@ int gm_jacobian(gm_ctx *ctx, const gm_model *model, const gm_batch *batch,
  *     workgroup per fit; k > 1 = min(k, tiles) workgroups for every fit of at
  *     least team_min_tiles 32 x 32 tiles, one for the others.  Except at 1,
  *     workgroups of a launch without teams that have run out of fits make
- *     tiles for the fits still running (results the same bits);
+ *     tiles for the fits still running (results the same bits).  Such helpers
+ *     stay on their compute units, at most as many as the running fits have
+ *     tiles, so that kernels of other streams find less room until the last
+ *     fit ends than beside a launch at 1, which takes longer;
  *   team_min_tiles -- see team (0 = 1);
  *   team_wait_us -- bound of every wait between the workgroups of a team, in
  *     microseconds (0 = 20 s); a fit whose team passes it ends with

@@ -1230,7 +1230,10 @@ __device__ inline void boot_weights(const BootArgs &bt, int64_t pix0, float (&m)
 // by spin_limit all the same: past it the owner makes the tile itself and
 // leaves the slot for good (a late helper can then only write to that slot).
 // A helper leaves, and is no longer counted, when no fit ended and it found no
-// tile for idle_limit.
+// tile for idle_limit, and when the running fits have fewer tiles than there
+// are helpers: that gives its CU to the kernels of other streams (1,024 fits
+// of 64 x 64, one image batch on another stream: done after 3.3 ms without
+// helpers, 7.3 with all of them kept, 3.6 now; the fits 13.2, 7.2 and 7.4 ms).
 // The board is zeroed before every launch; slots past n_slots are never used.
 constexpr int kHelpSlots = 64;
 constexpr int kHelpRing = 16;
@@ -1432,8 +1435,9 @@ __device__ inline int help_next(HelpState &hp, int next, int ntiles, int &held, 
 }
 
 // Helper, wave 0: takes a tile of some open evaluation into hp; false when
-// every fit has ended, or when no fit ended and no tile was found for idle_limit.
-__device__ inline bool help_find(HelpState &hp, int n_entries, int64_t idle_limit)
+// every fit has ended, when the fits still running have work for fewer helpers
+// (keep for each), or when no fit ended and no tile was found for idle_limit.
+__device__ inline bool help_find(HelpState &hp, int n_entries, int keep, int64_t idle_limit)
 {
     static_assert(kHelpSlots == 64, "one lane per slot");
     HelpBoard *bd = hp.board;
@@ -1471,8 +1475,21 @@ __device__ inline bool help_find(HelpState &hp, int n_entries, int64_t idle_limi
                 return true;
             }
         } else {
-            // 14 us: hundreds of idle workgroups looking more often slow the others' accesses
-            for (int z = 0; z < 4; ++z) __builtin_amdgcn_s_sleep(127);
+            const int idle = uniform(agent_load(&bd->idle));
+            const int64_t use = (int64_t)keep * (n_entries - done);
+            if (idle > use) {
+                int go = 0;
+                if (lane == 0) {
+                    go = help_count(&bd->idle, -1) > use;
+                    help_count(go ? &bd->left : &bd->idle, 1);
+                }
+                if (uniform(go)) return false;
+            }
+            // 0.4 us, or 3.5 to 14 with more helpers: hundreds of idle workgroups looking more often
+            // slow the others' accesses, a few looking less often leave tiles waiting
+            if (idle <= 32) __builtin_amdgcn_s_sleep(16);
+            else
+                for (int z = 0; z < min(4, 1 + idle / 64); ++z) __builtin_amdgcn_s_sleep(127);
         }
     }
 }
@@ -1508,7 +1525,8 @@ __device__ __forceinline__ void evaluate(const double *u, const ModelArgs &ma, c
         __syncthreads();
     } else {
         // a fit of several tiles asks for helpers when there is one for every
-        // four running fits (fewer give back less than sharing costs)
+        // four running fits (512 bulge + disk fits of 128 x 128: 60 ms, with one for
+        // every fit 63, for every sixteen 60; 256 of 64-128 px at a side of 31: 36, 38, 36)
         if (hp && hp->board && tid == NT - 1) {
             const int running = hp->n_entries - agent_load(&hp->board->done);
             sh_help[0] = ntiles > 1 && 4 * agent_load(&hp->board->idle) >= running;
@@ -1921,7 +1939,7 @@ struct FitArgs {
     char *help_buf;
     int64_t help_stride;      // bytes of help_buf per slot
     int64_t idle_limit;       // helpers' wait for work
-    int help_slots;
+    int help_slots, help_keep;
     int grid_items;           // workgroups worth launching (at least the queue entries)
 };
 
@@ -2464,7 +2482,7 @@ __global__ __launch_bounds__(NT, min_wg<F>()) void lm_fit_kernel(ModelArgs ma, B
         for (;;) {
             if (helper) {
                 if (tid < 64) {
-                    const bool any = help_find(hp, fa.n_gal, fa.idle_limit);
+                    const bool any = help_find(hp, fa.n_gal, fa.help_keep, fa.idle_limit);
                     if (tid == 0) {
                         s.action = any ? ACT_EVAL : ACT_DONE;
                         s.help[0] = hp.slot;

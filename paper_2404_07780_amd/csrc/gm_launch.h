@@ -359,6 +359,7 @@ int run_fit(gm_ctx *c, const CallInfo &ci, const gm_fit_opts *o, double *params,
                 fa.help_buf = reinterpret_cast<char *>(hw) + bb;
                 fa.help_stride = (int64_t)help_slot_bytes<F>();
                 fa.help_slots = slots;
+                fa.help_keep = (int)most;         // helpers kept for each running fit
                 grid_items = (int)std::min<int64_t>(tiles * nb, 1 << 30);
             }
         }

@@ -1,7 +1,8 @@
 """The helpers of a launch, by their counts: they make tiles; with waits
 bounded at a microsecond evaluations go on without a tile that is late (the
 recovery: the fit's own workgroup makes it and the rest of its evaluations,
-the slot is given up), with the same bits."""
+the slot is given up), with the same bits; and helpers that the fits still
+running have no tiles for leave their compute units."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -42,3 +43,8 @@ def test_late_tiles_are_made_by_the_owner(k):
     for c in _fit(SIDES, k, 1, 3, max_iter=12):
         assert c["turned"] > 0 and c["lost"] > 0, c
 
+
+def test_helpers_without_work_leave():
+    print("help counts: more helpers than tiles", flush=True)
+    for c in _fit([(64, 64)] * 60, 15, 0, 8):
+        assert c["tiles"] > 0 and c["left"] > 0, c
