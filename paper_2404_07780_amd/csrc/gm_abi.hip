@@ -826,6 +826,7 @@ int gm_set_schedule(gm_ctx *ctx, const gm_model *model, int32_t psf_k, const gm_
 int gm_help_counts(gm_ctx *ctx, int32_t *counts_out)
 {
     if (!ctx || !counts_out) return GM_EINVAL;
+    Scoped sd(ctx->device);
     int32_t head[6] = {0, 0, 0, 0, 0, 0};        // the first words of the helpers' board
     if (ctx->help) {
         if (hipDeviceSynchronize() != hipSuccess) return GM_EHIP;
