@@ -8,16 +8,17 @@
 // small LDS table.  Each thread then owns a 1 x 4 strip of outputs of every
 // plane convolved with the PSF (true convolution, zero padding): the FP64
 // light by vector FMAs, the FP32 planes on the matrix cores, row segments and
-// taps from LDS; the results stay in registers.  When the planes of a model do not fit
-// LDS together (or fit only one workgroup per CU) they are processed in NG
-// groups, re-evaluating the profile per group (only the first group needs the
-// FP64 light).  The fitting kernel turns the convolved planes into residuals
-// and FP64 normal-equation sums without writing any image to memory.
+// taps from LDS (the FP64 light's taps at compiled sides above 15: scalar loads
+// from memory); the results stay in registers.  When the planes of a model do
+// not fit LDS together (or fit only one workgroup per CU) they are processed in
+// NG groups, re-evaluating the profile per group (only the first group needs
+// the FP64 light).  The fitting kernel turns the convolved planes into
+// residuals and FP64 normal-equation sums without writing any image to memory.
 //
 // gm_fit_batch runs one persistent kernel: each workgroup pulls galaxies, in
 // descending-cost order, from an atomic queue and runs the whole
-// Levenberg-Marquardt iteration for a galaxy; thread 0 does the FP64 damped
-// Cholesky solve and accept/reject between evaluations.
+// Levenberg-Marquardt iteration for a galaxy; its first two waves do the FP64
+// Cholesky solves and accept or reject between evaluations.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -446,35 +447,6 @@ __device__ inline void load_seg(const T *p, T *seg)
     }
 }
 
-// Taps v0 .. v1-1 of one PSF row against the segment elements e0 .. (e0 a
-// multiple of the 16-byte vector width): acc[t] += sum_v p[v] seg[KT-1-v+t].
-template <int KT, int V0, int V1, int E0, typename T, typename PR>
-__device__ inline void row_part(const T *rp, PR pr, T &a0, T &a1, T &a2, T &a3)
-{
-    constexpr int PER = 16 / sizeof(T);
-    constexpr int N = ((KT + 2 - V0) - E0 + 1 + PER - 1) / PER * PER;
-    T seg[N];
-    using V = typename std::conditional<sizeof(T) == 4, float4, double2>::type;
-    const V *vp = reinterpret_cast<const V *>(rp + E0);
-#pragma unroll
-    for (int q = 0; q < N / PER; ++q) {
-        V t = vp[q];
-        if constexpr (sizeof(T) == 4) {
-            seg[4 * q] = t.x; seg[4 * q + 1] = t.y; seg[4 * q + 2] = t.z; seg[4 * q + 3] = t.w;
-        } else {
-            seg[2 * q] = t.x; seg[2 * q + 1] = t.y;
-        }
-    }
-#pragma unroll
-    for (int v = V0; v < V1; ++v) {
-        const T pv = (T)pr[v];
-        a0 = fma(pv, seg[KT - 1 - v - E0], a0);
-        a1 = fma(pv, seg[KT - v - E0], a1);
-        a2 = fma(pv, seg[KT + 1 - v - E0], a2);
-        a3 = fma(pv, seg[KT + 2 - v - E0], a3);
-    }
-}
-
 // Any PSF side, FP64: element by element of the row segment, from the far end
 // (each accumulator then sees its taps in increasing order), the four taps an
 // element meets sliding through registers; PSF rows from LDS (psl).
@@ -560,11 +532,12 @@ __device__ inline void load_taps(const float *psl, int u, float (&tp)[KP])
 // with one rounding (also for denormals), and x runs downwards, so each
 // accumulator sees the products of the scalar loop in its order: the results
 // are the same bits (the extra products are 0 x finite; conv_group sees to
-// strips with infinite elements).  One instruction of 8
-// cycles replaces four FMAs, which a single wave per SIMD issues at best every
-// 5 cycles (two waves together: every 2.6); matrix and vector instructions of
-// two waves do not overlap (both measured), so what bounds the convolutions is
-// the FMA units.  Before (FMAs with the taps in registers) and now, ms: 2,048
+// strips with infinite elements).  One instruction replaces four FMAs: a single
+// wave per SIMD issues one every 9.0 cycles with two accumulators in turn
+// (conv_pair), every 8.5 with four (conv_quad), and an FMA every 4.9; two waves
+// together 4.5, 4.3 and 2.4.  Matrix and vector instructions of two waves do
+// not overlap (all measured), so what bounds the convolutions is the FMA
+// units.  Before (FMAs with the taps in registers) and now, ms: 2,048
 // masked cutouts of 48-256 px, side 25: 326 -> 229; 256 of 64-128 px, side 31
 // (any-side loops, taps and elements one by one before): 907 -> 301; 16,384 of
 // 64 x 64, side 15: 55.4 -> 52.8.
@@ -2353,8 +2326,12 @@ __device__ __forceinline__ void load_u(LMShared<F> &s, const ModelArgs &ma, cons
 // LDS (measured 1.38x faster Sersic fits at 64 x 64, PSF side 15), and the
 // matrix instructions' accumulators stay in VGPRs: with more registers allowed
 // the compiler puts them into AGPRs, with copies in the convolution loops.
-// The one-component families fit this budget at every PSF side without spills
-// inside loops; the two-component models' normal-equation accumulators do not.
+// Most one-component fits meet this budget with a few spilled registers outside
+// their loops; those with nine and ten variables (boxy, tilted sky, free King
+// and Ferrer) spill 20 to 60 at a side of 15, some of them inside, and are
+// faster so than with one workgroup per CU all the same (1,024 boxy fits of
+// 64 x 64, eight trials: 4.8 -> 4.5 ms; tilted sky: 3.6 -> 2.95).  The two-component
+// models' normal-equation accumulators do not fit.
 template <class F>
 __host__ __device__ constexpr int min_wg()
 {
