@@ -349,11 +349,13 @@ int run_fit(gm_ctx *c, const CallInfo &ci, const gm_fit_opts *o, double *params,
                 tiles += t;
                 most = std::max(most, t);
             }
-            if (most > 1 && ci.team != 1) {
-                void *hw = nullptr;
-                const int slots = std::min(nfit, kHelpSlots);
-                const size_t bb = (sizeof(HelpBoard) + 255) & ~(size_t)255;
-                if ((rc = ensure_help(c, bb + help_slot_bytes<F>() * slots, &hw))) return rc;
+            void *hw = nullptr;
+            const int slots = std::min(nfit, kHelpSlots);
+            const size_t bb = (sizeof(HelpBoard) + 255) & ~(size_t)255;
+            rc = most > 1 && ci.team != 1 ? ensure_help(c, bb + help_slot_bytes<F>() * slots, &hw) : GM_OK;
+            if (rc == GM_ENOMEM) (void)hipGetLastError();        // the fits do without
+            else if (rc) return rc;
+            if (hw) {
                 board = reinterpret_cast<HelpBoard *>(hw);
                 fa.help = board;
                 fa.help_buf = reinterpret_cast<char *>(hw) + bb;
