@@ -532,15 +532,15 @@ __device__ inline void load_taps(const float *psl, int u, float (&tp)[KP])
 // with one rounding (also for denormals), and x runs downwards, so each
 // accumulator sees the products of the scalar loop in its order: the results
 // are the same bits (the extra products are 0 x finite; conv_group sees to
-// strips with infinite elements).  One instruction replaces four FMAs: a single
-// wave per SIMD issues one every 9.0 cycles with two accumulators in turn
-// (conv_pair), every 8.5 with four (conv_quad), and an FMA every 4.9; two waves
-// together 4.5, 4.3 and 2.4.  Matrix and vector instructions of two waves do
-// not overlap (all measured), so what bounds the convolutions is the FMA
-// units.  Before (FMAs with the taps in registers) and now, ms: 2,048
-// masked cutouts of 48-256 px, side 25: 326 -> 229; 256 of 64-128 px, side 31
-// (any-side loops, taps and elements one by one before): 907 -> 301; 16,384 of
-// 64 x 64, side 15: 55.4 -> 52.8.
+// strips with infinite elements).  A SIMD issues one instruction every 8.3
+// cycles (a wave alone: 9.0 with two accumulators in turn, conv_pair, 8.5 with
+// four, conv_quad), which replaces four FMAs at 2.5 cycles each (a wave alone:
+// 4.9); matrix and vector instructions of two waves do not overlap (all
+// measured), so what bounds the convolutions is the FMA
+// units.  Before (FMAs with the taps in registers) and now, ms: 2,048 masked
+// cutouts of 48-256 px, side 25: 326 -> 229; 256 of 64-128 px, side 31 (any-side
+// loops, taps and elements one by one before): 907 -> 301; 16,384 of 64 x 64,
+// side 15: 55.4 -> 52.8.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <int ABID>
